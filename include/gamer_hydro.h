@@ -80,8 +80,10 @@ typedef struct gamer_opts {
      * compiler may contract multiply-adds differently). */
     int32_t variant;
     /* Work-groups launched: 0 launches one per group (periodic entry points:
-     * one per z segment, see zseg); g > 0 launches at most g persistent
-     * work-groups that stride over the groups (segments). */
+     * one per z segment, see zseg), or, for batches too small to fill the chip,
+     * one per z part of a group (2 to 16 parts; with group_stats a second small
+     * launch forms the stats); g > 0 launches at most g persistent work-groups
+     * that stride over the groups (segments).  The results do not depend on it. */
     int32_t grid;
     /* Variables the slopes are limited in: GAMER_LIMIT_PRIMITIVE (0, the
      * default) limits each primitive variable; GAMER_LIMIT_CHARACTERISTIC (1)

@@ -173,6 +173,7 @@ int solve_common(const S *in, int64_t n, const int8_t *level, const double *dt_d
     p.n_levels = dt_dev ? n_levels : 1;
     p.char_limiting = limiting;
     p.zseg = 1;
+    p.nsub = 0;
     p.bad = bad;
     return check_hip(launch_solve<S, T>(p, variant, grid, stream), "solver launch");
 }
@@ -214,6 +215,7 @@ int periodic_common(const S *state, int gx, int gy, int gz, const double *dt_dev
     p.n_levels = 1;
     p.char_limiting = limiting;
     p.zseg = zseg == 0 ? auto_zseg(gx, gy, gz) : (zseg < gz ? zseg : gz);
+    p.nsub = zseg == 0 ? 0 : 1;  // an explicit zseg asks for whole groups
     p.bad = bad;
     return check_hip(launch_solve<S, T>(p, variant, grid, g_stream), "solver launch");
 }

@@ -42,6 +42,8 @@ struct SolveParams {
     int char_limiting;  // 0: limit primitive variables, 1: characteristic variables
     int zseg;           // periodic input: groups per z segment of a column that one
                         // work-group sweeps in one pass (>= 1)
+    int nsub;           // equal z parts a group is cut into, each swept by its own
+                        // work-group (1: whole groups; 0: the launcher's choice)
     // device counters or nullptr: [0] output cells that are not physical or not
     // finite, [1] groups whose level byte lies outside [0, n_levels)
     unsigned long long *bad;

@@ -140,13 +140,19 @@ __device__ __forceinline__ int plane_pos(int q) {
     return ((r >> 2) + NG) * NP + (col < NG ? col : col + NI);
 }
 
+// Most z parts of a group: each has a 32-bit slot in the group's 64 bytes of
+// stats for its fallback counts (predictions in the low half, at most 320 x 8 +
+// 512 with two parts; faces in the high half, at most 800 x 8 + 256).
+constexpr int MAX_PARTS = 16;
+static_assert(MAX_PARTS * sizeof(unsigned) <= NSTAT * sizeof(double), "a slot per part");
+
 // One work-group of NT threads advances one group at a time (grid-stride).
 //  NT = 320: threads 0..255 own the interior columns, 256..319 the ghost-layer
 //            cells of every plane (5 waves).
 //  NT = 256: threads own the interior columns; in plane k the wave k mod 4 also
 //            computes the 64 ghost-layer cells in a second round (4 waves, one
 //            per SIMD).
-template <typename S_, typename T, int NT, int WAVES, bool PERIODIC, bool CHAR>
+template <typename S_, typename T, int NT, int WAVES, bool PERIODIC, bool CHAR, bool SUB>
 __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT), amdgpu_waves_per_eu(WAVES, 8)))
 void solve_kernel(SolveParams<S_> P) {
     static_assert(NT == 320 || NT == 256, "work-group shape");
@@ -163,27 +169,48 @@ void solve_kernel(SolveParams<S_> P) {
 
     // A unit is one group of padded input, or, for periodic input, a run of
     // nseg groups along z of one (x, y) column, swept as one sequence of planes
-    // (units numbered column fastest, then z segment).
+    // (units numbered column fastest, then z segment); or, with nsub > 1, one of
+    // nsub equal z parts of a group (the parts of a group numbered together).
     const int64_t cols = PERIODIC ? int64_t(P.gx) * P.gy : 1;
-    const int64_t n_units = PERIODIC ? cols * ((P.gz + P.zseg - 1) / P.zseg) : P.n_groups;
+    const int nsub = SUB ? P.nsub : 1;
+    const int64_t n_units = SUB && nsub > 1 ? P.n_groups * nsub
+                            : PERIODIC     ? cols * ((P.gz + P.zseg - 1) / P.zseg)
+                                           : P.n_groups;
     for (int64_t slot = blockIdx.x; slot < n_units; slot += gridDim.x) {
         const int64_t unit = xcd_group(slot, n_units);
         int bx = 0, by = 0, bz = 0, nseg = 1;
         int64_t g = unit;  // the unit's first group; group q of the unit is g + q * cols
+        [[maybe_unused]] int z0 = 0;  // the group plane the unit starts at (0 unless nsub > 1)
+        if constexpr (SUB) {
+            if (nsub > 1) {
+                g = unit / nsub;
+                z0 = int(unit - g * nsub) * (NI / nsub);
+            }
+        }
         if (PERIODIC) {
-            const int64_t col = unit % cols;
+            const int64_t row = SUB ? g : unit;
+            const int64_t col = row % cols;
             bx = int(col % P.gx);
             by = int(col / P.gx);
-            bz = int(unit / cols) * P.zseg;
+            bz = int(row / cols) * P.zseg;
             nseg = P.gz - bz < P.zseg ? P.gz - bz : P.zseg;
             g = col + cols * bz;
         }
-        const int nplanes = NI * nseg;  // interior planes 0 .. nplanes-1 of the unit
+        // interior planes 0 .. nplanes-1 of the unit
+        const int nplanes = SUB && nsub > 1 ? NI / nsub : NI * nseg;
+        // whether the unit's lower and upper ends are ends of its group (or groups)
+        const bool first = !SUB || z0 == 0, last = !SUB || nsub <= 1 || z0 + nplanes == NI;
+        auto zg = [&](int k) -> int {  // unit plane k counted from the first group's plane 0
+            if constexpr (SUB)
+                return z0 + k;
+            else
+                return k;
+        };
         double dt = P.dt, dh = P.dh;
         if (P.dt_dev && !level_dt(P.level, g, P.n_levels, P.dt_dev, P.dh_dev, dt, dh)) {
             // a level byte out of range: the group runs on NaN dt and dh (its
             // output and stats come out NaN) and is counted once
-            if (P.bad && t == 0) atomicAdd(P.bad + 1, 1ull);
+            if (P.bad && t == 0 && (!SUB || first)) atomicAdd(P.bad + 1, 1ull);
         }
         const double dtdh = dt / dh;
         const double hdtdh = 0.5 * dtdh;  // the Roe fluxes below are kept doubled (2F)
@@ -210,8 +237,8 @@ void solve_kernel(SolveParams<S_> P) {
         };
         // z part, and the base pointer of a plane for the x/y group part 0
         auto plane_base = [&](int kp) -> const S_ * {
-            if (!PERIODIC) return P.in + g * GIN + kp * NPL;
-            int Z = bz * NI + kp - NG;
+            if (!PERIODIC) return P.in + g * GIN + zg(kp) * NPL;
+            int Z = bz * NI + zg(kp) - NG;
             const int NZ = P.gz * NI;
             Z = Z < 0 ? Z + NZ : (Z >= NZ ? Z - NZ : Z);
             return P.in + int64_t(P.gx) * P.gy * (Z / NI) * GOUT + (Z % NI) * (NI * NI);
@@ -336,8 +363,8 @@ void solve_kernel(SolveParams<S_> P) {
         // stores (memory operations complete in issue order).
         for (int k = -1; k <= nplanes; ++k) {
             // plane k of the unit is plane kl of its group gk (k in 0 .. nplanes-1;
-            // with padded input, the group itself and k)
-            const int kq = PERIODIC ? k >> 4 : 0, kl = PERIODIC ? k & 15 : k;
+            // with padded input, the group itself)
+            const int kq = PERIODIC ? zg(k) >> 4 : 0, kl = PERIODIC ? zg(k) & 15 : zg(k);
             const int64_t gk = PERIODIC ? g + int64_t(kq) * cols : g;
             const bool ahead = k + 2 <= nplanes + 1;
             if (ahead) fetch(k + 2);
@@ -411,7 +438,7 @@ void solve_kernel(SolveParams<S_> P) {
                     // first-order fallback: every face of the cell takes the cell average
                     if constexpr (PERIODIC)
                         step |= round == 0 ? 1 : 2;
-                    else
+                    else if (!SUB || ((k >= 0 || first) && (k < nplanes || last)))
                         ++n_pred;
 #pragma unroll
                     for (int v = 0; v < NV; ++v) {
@@ -468,7 +495,7 @@ void solve_kernel(SolveParams<S_> P) {
                     const bool fb = roe_dir<2, true>(zp, zm, c, fzn);
                     if constexpr (PERIODIC)
                         step |= int(fb) << 2;
-                    else
+                    else if (!SUB || k < nplanes || last)
                         n_roe += fb;
                     if (P.flux) {
                         const int off = jj * NI + ii;
@@ -485,8 +512,8 @@ void solve_kernel(SolveParams<S_> P) {
 #pragma unroll
                                 for (int v = 0; v < NV; ++v) dst[v * NINNER] = S_(c.half * fzn[v]);
                             }
-                        } else if ((k & 7) == 0) {
-                            S_ *dst = P.flux + g * GFLX + ((2 * 3 + (k >> 3)) * NV) * NINNER + off;
+                        } else if ((kl & 7) == 0 && (!SUB || k < nplanes || last)) {
+                            S_ *dst = P.flux + g * GFLX + ((2 * 3 + (kl >> 3)) * NV) * NINNER + off;
 #pragma unroll
                             for (int v = 0; v < NV; ++v) dst[v * NINNER] = S_(c.half * fzn[v]);
                         }
@@ -578,12 +605,12 @@ void solve_kernel(SolveParams<S_> P) {
             constexpr bool EARLY = sizeof(T) == 4;
             S_ uold[NV];
             // plane k-1 of the unit: plane ul of group gu
-            const int ul = PERIODIC ? (k - 1) & 15 : k - 1;
-            const int64_t gu = PERIODIC ? g + int64_t((k - 1) >> 4) * cols : g;
+            const int ul = PERIODIC ? zg(k - 1) & 15 : zg(k - 1);
+            const int64_t gu = PERIODIC ? g + int64_t(zg(k - 1) >> 4) * cols : g;
             auto load_old = [&]() {
                 // an interior cell: in the group's own block in both input kinds
                 const S_ *src = PERIODIC ? P.in + gu * GOUT + ul * NINNER
-                                         : P.in + g * GIN + (k - 1 + NG) * NPL + NG * NP + NG;
+                                         : P.in + g * GIN + (zg(k - 1) + NG) * NPL + NG * NP + NG;
                 const unsigned off = PERIODIC ? unsigned(t) : unsigned(jj * NP + ii);
 #pragma unroll
                 for (int v = 0; v < NV; ++v) uold[v] = at(src + v * VSTRIDE, off);
@@ -629,10 +656,10 @@ void solve_kernel(SolveParams<S_> P) {
                 // this step's fallbacks to the groups they belong to (see `step`)
                 const int pi = step & 1, pr = (step >> 1) & 1, rz = (step >> 2) & 1, rxy = step >> 3;
                 if (k < 0) {
-                    n_pred += pi;  // the first group's ghost plane -1
+                    n_pred += !SUB || first ? pi : 0;  // the first group's ghost plane -1
                 } else if (k == nplanes) {
-                    n_pred += pi;  // the last group's ghost plane 16 and face 16
-                    n_roe += rz;
+                    n_pred += !SUB || last ? pi : 0;  // the last group's ghost plane 16 and face 16
+                    n_roe += !SUB || last ? rz : 0;
                 } else if (kl == 0 && k > 0) {
                     n_pred += pi;  // group kq - 1: ghost plane 16, face 16
                     n_roe += rz;
@@ -664,7 +691,21 @@ void solve_kernel(SolveParams<S_> P) {
         }
 
         if (P.bad && n_bad) atomicAdd(P.bad, (unsigned long long)n_bad);
-        if (P.stats) {
+        if (SUB && P.stats && nsub > 1) {
+            // the part's fallback counts, packed into its slot of the group's
+            // stats; part_stats_kernel turns the slots into the stats
+            unsigned sum = unsigned(n_pred) + (unsigned(n_roe) << 16);
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) sum += __shfl_down(sum, off, 64);
+            unsigned *red = reinterpret_cast<unsigned *>(&S.w[0][0][0]);  // free now (B3 of the last step passed)
+            if ((t & 63) == 0) red[wave] = sum;
+            __syncthreads();
+            if (t == 0) {
+                for (int w = 1; w < NT / 64; ++w) sum += red[w];
+                reinterpret_cast<unsigned *>(P.stats + g * NSTAT)[z0 / nplanes] = sum;
+            }
+            __syncthreads();
+        } else if (P.stats) {
             double all[NSTAT] = {st[0], st[1], st[2], st[3], st[4], st[5], double(n_pred),
                                  double(n_roe)};
             // S.w is free now (B3 of the last step passed); reuse it for the reduction
@@ -674,6 +715,38 @@ void solve_kernel(SolveParams<S_> P) {
             __syncthreads();
         }
     }
+}
+
+// The stats of groups that were advanced in parts: 32-bit slots 0 .. nsub-1 of
+// a group's stats hold its parts' fallback counts; the sums and the signal
+// speed are taken from the new state as a whole group's sweep takes them (thread
+// (i, j) folds its column upwards, then the fixed-order reduction), so the
+// stats do not depend on the split.
+template <typename S_, typename T>
+__global__ __launch_bounds__(NINNER) void part_stats_kernel(const S_ *__restrict__ out, double gamma, int nsub,
+                                                            double *__restrict__ stats) {
+    __shared__ double red[NINNER * NSTAT];
+    const int t = threadIdx.x;
+    const int64_t g = blockIdx.x;
+    const Consts<T> c = make_consts<T>(gamma, 1.5);
+    const S_ *src = out + g * GOUT + t;
+    double st[NSTAT] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (t < nsub) {
+        const unsigned q = reinterpret_cast<const unsigned *>(stats + g * NSTAT)[t];
+        st[6] = double(q & 0xffffu);
+        st[7] = double(q >> 16);
+    }
+#pragma unroll 8
+    for (int k = 0; k < NI; ++k) {
+        S_ u[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            u[v] = src[v * (NI * NINNER) + k * NINNER];
+            st[v] += double(u[v]);
+        }
+        st[5] = max_nan(st[5], double(signal_speed(T(u[0]), T(u[1]), T(u[2]), T(u[3]), T(u[4]), c)));
+    }
+    block_reduce_stats<NINNER>(st, red, stats + g * NSTAT);
 }
 
 static_assert(sizeof(Lds<float>::w) >= 320 * NSTAT * sizeof(double),
@@ -695,43 +768,78 @@ int solve_variant_shape(int v, int *threads, int *waves) {
 }
 
 namespace {
-template <typename S_, typename T, int V, bool CHAR>
+template <typename S_, typename T, int V, bool CHAR, bool SUB>
 void launch_shape(const SolveParams<S_> &p, dim3 blocks, hipStream_t s) {
     constexpr Shape sh = Variants<T>::shape[V];
     if (p.gx > 0)
-        hipLaunchKernelGGL((solve_kernel<S_, T, sh.threads, sh.waves, true, CHAR>), blocks,
+        hipLaunchKernelGGL((solve_kernel<S_, T, sh.threads, sh.waves, true, CHAR, SUB>), blocks,
                            dim3(sh.threads), 0, s, p);
     else
-        hipLaunchKernelGGL((solve_kernel<S_, T, sh.threads, sh.waves, false, CHAR>), blocks,
+        hipLaunchKernelGGL((solve_kernel<S_, T, sh.threads, sh.waves, false, CHAR, SUB>), blocks,
                            dim3(sh.threads), 0, s, p);
 }
-template <typename S_, typename T, int V>
+template <typename S_, typename T, int V, bool SUB = false>
 void launch_variant(const SolveParams<S_> &p, dim3 blocks, hipStream_t s) {
     if (p.char_limiting)
-        launch_shape<S_, T, V, true>(p, blocks, s);
+        launch_shape<S_, T, V, true, SUB>(p, blocks, s);
     else
-        launch_shape<S_, T, V, false>(p, blocks, s);
+        launch_shape<S_, T, V, false, SUB>(p, blocks, s);
+}
+}  // namespace
+
+namespace {
+// Equal z parts of a group that go to work-groups of their own when a batch of n
+// groups leaves the chip idle: the most for which every part still has a slot
+// (a CU holds three float or two double work-groups).  A group's sweep is one
+// chain of 18 plane steps, about 5 us each however empty the chip is, and a
+// part of NI / s planes takes NI / s + 2 of them.  Measured per step (periodic,
+// reduce included): 8 groups FP64 150 -> 44 us in 8 parts; 64 groups FP32 100
+// -> 39 in 8; 125 groups FP64 122 -> 74 in 4 (81 in 8, which no longer fit);
+// 216 groups FP32 101 -> 74 in 2 (77 in 4); 512 groups FP32 116 -> 125 in 2.
+template <typename T>
+int choose_parts(int64_t n) {
+#ifdef FORCE_NSUB
+    return FORCE_NSUB;
+#endif
+    constexpr int64_t slots = 256 * (sizeof(T) == 4 ? 3 : 2);
+    for (int s = MAX_PARTS; s > 1; s /= 2)
+        if (n * s <= slots) return s;
+    return 1;
 }
 }  // namespace
 
 // Storage type S_, arithmetic type T (float or S_).  variant < 0 selects the
-// default; grid <= 0 launches one work-group per group, grid > 0 a persistent
-// grid that strides over the groups.
+// default; grid <= 0 launches one work-group per group (or part of one, where
+// the caller leaves p.nsub at 0), grid > 0 a persistent grid that strides over
+// the groups.  Batches small enough to be split run the kernel that can split
+// (SUB) whatever the grid and zseg, so that these do not change the results (the
+// compiler may contract multiply-adds differently in the other one, which
+// spares large batches the parts' bookkeeping, 2% of a step).
 template <typename S_, typename T>
-hipError_t launch_solve(const SolveParams<S_> &p, int variant, int64_t grid, hipStream_t s) {
+hipError_t launch_solve(const SolveParams<S_> &params, int variant, int64_t grid, hipStream_t s) {
+    SolveParams<S_> p = params;
     if (p.n_groups <= 0) return hipSuccess;
+    const bool sub = variant <= 0 && choose_parts<T>(p.n_groups) > 1;
+    if (p.nsub == 0) p.nsub = sub && grid <= 0 && p.zseg == 1 ? choose_parts<T>(p.n_groups) : 1;
+    if (p.nsub < 1 || p.nsub > MAX_PARTS || NI % p.nsub || (p.nsub > 1 && p.zseg != 1)) return hipErrorInvalidValue;
     // work units: groups, or z segments of the columns of a periodic grid
     int64_t units = p.n_groups;
     if (p.gx > 0) {
         if (p.zseg < 1 || p.zseg > p.gz) return hipErrorInvalidValue;
         units = int64_t(p.gx) * p.gy * ((p.gz + p.zseg - 1) / p.zseg);
     }
+    if (p.nsub > 1) units = p.n_groups * p.nsub;
     const int64_t max_grid = int64_t(1) << 30;
     int64_t g = grid > 0 ? (grid < units ? grid : units) : units;
     if (g > max_grid) g = max_grid;
     const dim3 blocks = dim3(unsigned(g));
     switch (variant < 0 ? 0 : variant) {
-        case 0: launch_variant<S_, T, 0>(p, blocks, s); break;
+        case 0:
+            if (sub)
+                launch_variant<S_, T, 0, true>(p, blocks, s);
+            else
+                launch_variant<S_, T, 0>(p, blocks, s);
+            break;
         case 1: launch_variant<S_, T, 1>(p, blocks, s); break;
         case 2:
             if constexpr (Variants<T>::count > 2) {
@@ -741,6 +849,9 @@ hipError_t launch_solve(const SolveParams<S_> &p, int variant, int64_t grid, hip
             return hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
     }
+    if (p.nsub > 1 && p.stats)
+        hipLaunchKernelGGL((part_stats_kernel<S_, T>), dim3(unsigned(p.n_groups)), dim3(NINNER), 0, s, p.out, p.gamma,
+                           p.nsub, p.stats);
     return hipGetLastError();
 }
 
