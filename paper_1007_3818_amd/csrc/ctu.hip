@@ -115,9 +115,9 @@ __device__ __forceinline__ bool predict_from(const T W0[NV], const T wl[NV], con
     T wm[NV], wp[NV], fm[NV], fp[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        const T dw = limiter(W0[v] - wl[v], wr[v] - W0[v], c.theta);
-        wm[v] = W0[v] - c.half * dw;
-        wp[v] = W0[v] + c.half * dw;
+        const T dw = limiter(W0[v] - wl[v], wr[v] - W0[v], c.k1);  // the slope over theta
+        wm[v] = W0[v] - c.ht * dw;
+        wp[v] = W0[v] + c.ht * dw;
     }
     cons_prim(wm, c, um);
     cons_prim(wp, c, up);

@@ -3,6 +3,17 @@
 // limiters, physical fluxes, the Hancock predictor, Roe's flux with the
 // Harten-Hyman entropy fix and the HLLE fallback, and the fixed-order
 // per-group stats reduction.
+//
+// The kernels that use these functions are bound by VALU issue (float) or close
+// to it (double), so the forms below are chosen for their instruction count.
+// Each function contracts multiply-adds within one expression only (fp
+// contract(on)), which makes its rounding a property of the source: a face state
+// or a face flux has the same bits in every kernel and at every place it is
+// inlined, whatever the register budget.  Against the plain forms (slopes with
+// theta multiplied in, physical fluxes formed and then subtracted, the
+// dissipation summed over all five waves; euler_mixed.h) the 256^3 padded step
+// took 577 -> 556 us in float (1,247 -> 1,160 vector instructions per cell) and
+// 1,070 -> 1,024 us in double.
 #pragma once
 
 #include "device_math.h"
@@ -13,28 +24,31 @@ namespace {
 
 template <typename T>
 __device__ __forceinline__ bool physical(const T u[NV]) {
+#pragma clang fp contract(on)
     // rho > 0 and p > 0  <=>  rho > 0 and 2 rho E > |m|^2
-    return u[0] > T(0) && T(2) * u[0] * u[4] > u[1] * u[1] + u[2] * u[2] + u[3] * u[3];
+    return u[0] > T(0) && (u[0] + u[0]) * u[4] > u[1] * u[1] + u[2] * u[2] + u[3] * u[3];
 }
 
-// Generalised minmod: 0 at extrema (a b <= 0), else sign(a) min(theta|a|,
-// theta|b|, |a+b|/2).  In float it is evaluated as med3(theta a,
-// med3(theta b, (a+b)/2, 0), 0): the median with 0 is the two-argument minmod,
-// and nesting it gives the same value bitwise whenever a and b share a sign
-// (and 0 otherwise); only an a b that underflows to 0 would differ.
-__device__ __forceinline__ float limiter(float a, float b, float theta) {
-    const float inner = __builtin_amdgcn_fmed3f(theta * b, 0.5f * (a + b), 0.0f);
-    return __builtin_amdgcn_fmed3f(theta * a, inner, 0.0f);
+// Generalised minmod over theta: 0 at extrema (a b <= 0), else sign(a) min(|a|,
+// |b|, |a+b| / (2 theta)); k1 = 1 / (2 theta).  The slope is theta times this, and
+// the factor is taken where the face values are formed (c.ht = theta / 2), which
+// spares two multiplications per slope.  In float it is evaluated as med3(a,
+// med3(b, k1 (a+b), 0), 0): the median with 0 is the two-argument minmod, and
+// nesting it gives the same value bitwise whenever a and b share a sign (and 0
+// otherwise).
+__device__ __forceinline__ float limiter(float a, float b, float k1) {
+#pragma clang fp contract(on)
+    const float inner = __builtin_amdgcn_fmed3f(b, k1 * (a + b), 0.0f);
+    return __builtin_amdgcn_fmed3f(a, inner, 0.0f);
 }
 // In double, without a branch: bs = b with the sign of a is positive exactly
-// when a and b share a sign, and then |a| + bs = |a + b|; otherwise theta bs <= 0
-// and the clamp at 0 gives a zero slope (of either sign).  The min is taken
-// over the same three values as in the definition, so a nonzero slope is the
-// same bitwise.
-__device__ __forceinline__ double limiter(double a, double b, double theta) {
+// when a and b share a sign, and then |a| + bs = |a + b|; otherwise bs <= 0 and
+// the clamp at 0 gives a zero slope (of either sign).
+__device__ __forceinline__ double limiter(double a, double b, double k1) {
+#pragma clang fp contract(on)
     const double aa = fabs(a);
     const double bs = __builtin_copysign(1.0, a) * b;
-    const double m = fmin(theta * aa, fmin(theta * bs, 0.5 * (aa + bs)));
+    const double m = fmin(aa, fmin(bs, k1 * (aa + bs)));
     return __builtin_copysign(fmax(m, 0.0), a);
 }
 
@@ -47,24 +61,27 @@ __device__ __forceinline__ double limiter(double a, double b, double theta) {
 //   u (entropy): l = (1, 0, 0, 0, -1/c^2), r = (1, 0, 0, 0, 0)
 //   u (shear, two): unit vectors of the transverse velocities
 //   u + c: l = (0, rho/2c, 0, 0, 1/2c^2), r = (1, c/rho, 0, 0, c^2)
-// h = rho/(2c), q = 1/(2c^2), cr = c/rho, c2 = c^2 of the cell.
+// h = rho/(2c), q = 1/(2c^2), cr = c/rho, c2 = c^2 of the cell.  Slopes over
+// theta, as the limiter gives them.
 template <int D, typename T>
 __device__ __forceinline__ void char_slope(const T a[NV], const T b[NV], T h, T q, T cr, T c2,
-                                           T theta, T dw[NV]) {
+                                           T k1, T dw[NV]) {
+#pragma clang fp contract(on)
     constexpr int N = 1 + D, T1 = D == 0 ? 2 : 1, T2 = D == 2 ? 2 : 3;
-    const T m0 = limiter(q * a[4] - h * a[N], q * b[4] - h * b[N], theta);
-    const T m1 = limiter(a[0] - T(2) * q * a[4], b[0] - T(2) * q * b[4], theta);
-    const T m4 = limiter(q * a[4] + h * a[N], q * b[4] + h * b[N], theta);
+    const T m0 = limiter(q * a[4] - h * a[N], q * b[4] - h * b[N], k1);
+    const T m1 = limiter(a[0] - T(2) * q * a[4], b[0] - T(2) * q * b[4], k1);
+    const T m4 = limiter(q * a[4] + h * a[N], q * b[4] + h * b[N], k1);
     dw[0] = m0 + m1 + m4;
     dw[N] = cr * (m4 - m0);
-    dw[T1] = limiter(a[T1], b[T1], theta);
-    dw[T2] = limiter(a[T2], b[T2], theta);
+    dw[T1] = limiter(a[T1], b[T1], k1);
+    dw[T2] = limiter(a[T2], b[T2], k1);
     dw[4] = c2 * (m0 + m4);
 }
 
 // Physical flux along direction D of a primitive state (rho, u_x, u_y, u_z, p).
 template <int D, typename T>
 __device__ __forceinline__ void flux_prim(const T w[NV], const Consts<T> &c, T f[NV]) {
+#pragma clang fp contract(on)
     const T un = w[1 + D];
     const T e = w[4] * c.igm1 + c.half * w[0] * (w[1] * w[1] + w[2] * w[2] + w[3] * w[3]);
     const T mn = w[0] * un;
@@ -79,6 +96,7 @@ __device__ __forceinline__ void flux_prim(const T w[NV], const Consts<T> &c, T f
 // Conserved variables of a primitive state.
 template <typename T>
 __device__ __forceinline__ void cons_prim(const T w[NV], const Consts<T> &c, T u[NV]) {
+#pragma clang fp contract(on)
     u[0] = w[0];
     u[1] = w[0] * w[1];
     u[2] = w[0] * w[2];
@@ -86,58 +104,92 @@ __device__ __forceinline__ void cons_prim(const T w[NV], const Consts<T> &c, T u
     u[4] = w[4] * c.igm1 + c.half * w[0] * (w[1] * w[1] + w[2] * w[2] + w[3] * w[3]);
 }
 
-// S += F_D(W0 - dW/2) - F_D(W0 + dW/2)
+// One direction D of the half-step prediction: the two face states W0 -+ dW/2
+// (dw: the slope over theta) as density, velocities, momentum along D and energy,
+// and their flux difference taken into the increment,
+//   S += F_D(minus) - F_D(plus),
+// product by product: every term but the pressure's is one multiply-add (the
+// pressure's is -dp of the slope), against a flux formed, subtracted and added.
+template <typename T>
+struct FacePair {
+    T rho[2], u[2][3], mn[2], e[2];
+};
 template <int D, typename T>
-__device__ __forceinline__ void flux_difference(const T W0[NV], const T dw[NV], const Consts<T> &c,
-                                                T Sv[NV]) {
-    T wm[NV], wp[NV], fm[NV], fp[NV];
+__device__ __forceinline__ void face_pair(const T W0[NV], const T dw[NV], const Consts<T> &c, T S[NV],
+                                          FacePair<T> &f) {
+#pragma clang fp contract(on)
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        wm[v] = W0[v] - c.half * dw[v];
-        wp[v] = W0[v] + c.half * dw[v];
+    for (int side = 0; side < 2; ++side) {
+        T w[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) w[v] = side ? W0[v] + c.ht * dw[v] : W0[v] - c.ht * dw[v];
+        const T r = w[0], p = w[4], un = w[1 + D];
+        const T mn = r * un;
+        const T e = (c.half * r) * (w[1] * w[1] + w[2] * w[2] + w[3] * w[3]) + p * c.igm1;
+        f.rho[side] = r;
+        f.mn[side] = mn;
+        f.e[side] = e;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) f.u[side][q] = w[1 + q];
+        if (D == 0 && side == 0) {
+            S[0] = mn;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) S[1 + q] = mn * w[1 + q];
+            S[4] = (e + p) * un;
+        } else if (side == 0) {
+            S[0] = S[0] + mn;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) S[1 + q] = S[1 + q] + mn * w[1 + q];
+            S[4] = S[4] + (e + p) * un;
+        } else {
+            S[0] = S[0] - mn;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) S[1 + q] = S[1 + q] - mn * w[1 + q];
+            S[4] = S[4] - (e + p) * un;
+        }
     }
-    flux_prim<D>(wm, c, fm);
-    flux_prim<D>(wp, c, fp);
-#pragma unroll
-    for (int v = 0; v < NV; ++v) Sv[v] += fm[v] - fp[v];
+    S[1 + D] = S[1 + D] - c.theta * dw[4];
 }
 
 // Half-step prediction of one cell (conservative Hancock step, all three
 // directions): face values W0 -+ dW_d/2, the common increment
 //   S = dt/(2dh) sum_d [F_d(W0 - dW_d/2) - F_d(W0 + dW_d/2)],
 // and Ub[d][0] (minus face), Ub[d][1] (plus face) = cons(W0 -+ dW_d/2) + S.
-// Returns false if any of the six has rho <= 0 or p <= 0.
+// dW: the slopes over theta.  Returns false if any of the six has rho <= 0 or
+// p <= 0.
 template <typename T>
 __device__ __forceinline__ bool predict(const T W0[NV], const T dW[3][NV], T hdt,
                                         const Consts<T> &c, T Ub[3][2][NV]) {
-    T Sv[NV] = {T(0), T(0), T(0), T(0), T(0)};
-    flux_difference<0>(W0, dW[0], c, Sv);
-    flux_difference<1>(W0, dW[1], c, Sv);
-    flux_difference<2>(W0, dW[2], c, Sv);
+#pragma clang fp contract(on)
+    T S[NV];
+    FacePair<T> f[3];
+    face_pair<0>(W0, dW[0], c, S, f[0]);
+    face_pair<1>(W0, dW[1], c, S, f[1]);
+    face_pair<2>(W0, dW[2], c, S, f[2]);
 #pragma unroll
-    for (int v = 0; v < NV; ++v) Sv[v] *= hdt;
+    for (int v = 0; v < NV; ++v) S[v] = S[v] * hdt;
     bool ok = true;
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
 #pragma unroll
         for (int side = 0; side < 2; ++side) {
-            T wf[NV];
+            T *U = Ub[d][side];
+            U[0] = f[d].rho[side] + S[0];
 #pragma unroll
-            for (int v = 0; v < NV; ++v) wf[v] = W0[v] + T(side ? 1 : -1) * (c.half * dW[d][v]);
-            cons_prim(wf, c, Ub[d][side]);
-#pragma unroll
-            for (int v = 0; v < NV; ++v) Ub[d][side][v] += Sv[v];
-            ok = ok && physical(Ub[d][side]);
+            for (int q = 0; q < 3; ++q)
+                U[1 + q] = q == d ? f[d].mn[side] + S[1 + q] : S[1 + q] + f[d].rho[side] * f[d].u[side][q];
+            U[4] = f[d].e[side] + S[4];
+            ok = ok && physical(U);
         }
     }
     return ok;
 }
 
-
 // Physical flux of a rotated conserved state (normal = component 1), given
 // its normal velocity and pressure.
 template <typename T>
 __device__ __forceinline__ void rot_flux(const T U[NV], T un, T p, T F[NV]) {
+#pragma clang fp contract(on)
     F[0] = U[1];
     F[1] = U[1] * un + p;
     F[2] = U[2] * un;
@@ -149,6 +201,7 @@ __device__ __forceinline__ void rot_flux(const T U[NV], T un, T p, T F[NV]) {
 template <typename T>
 __device__ __forceinline__ void hlle(const T L[NV], const T R[NV], T uL, T pL, T uR, T pR, T SL, T SR,
                                   T F[NV]) {
+#pragma clang fp contract(on)
     T FL[NV], FR[NV];
     rot_flux(L, uL, pL, FL);
     rot_flux(R, uR, pR, FR);
@@ -168,8 +221,10 @@ __device__ __forceinline__ void hlle(const T L[NV], const T R[NV], T uL, T pL, T
 // Roe flux between rotated conserved states (component 1 = normal momentum).
 // Harten-Hyman entropy fix on the acoustic waves, HLLE when a2 <= 0 or an
 // intermediate state is unphysical.  Returns true when HLLE was used.
-// Arithmetic layout: one reciprocal square root per side gives sqrt(rho) and
-// 1/rho; one of a2 gives a and 1/a; the intermediate states' positivity and
+// Arithmetic layout: in float one reciprocal square root per side gives
+// sqrt(rho) and 1/rho; in double, where it takes five more instructions and
+// sixteen cycles, one of the product rho_L rho_R gives both 1/rho and the Roe
+// weight sqrt(rho_L rho_R).  One of a2 gives a and 1/a; the intermediate states' positivity and
 // rho c come from Q = 2 rho E - |m|^2 (p > 0 <=> Q > 0, (rho c)^2 = gq Q), so
 // they need no reciprocal unless the entropy fix is active on that lane.  In
 // double, where a square root is a refined estimate of about fifteen
@@ -177,6 +232,11 @@ __device__ __forceinline__ void hlle(const T L[NV], const T R[NV], T uL, T pL, T
 // rho, (rho* c*)^2 = gq Q*), and the square roots are taken only on lanes where
 // the fix is active or HLLE is used; in float the square root is one hardware
 // instruction and the speeds are formed directly.
+// The dissipation sum_k |lambda_k| alpha_k K_k is taken as |u| (U_R - U_L), which
+// is |u| times all five waves, plus (|lambda_k| - |u|) alpha_k K_k of the two
+// acoustic waves: the three waves of speed u then need no strengths, and with
+// dp = (gamma-1)(dE - u.dm + |u|^2/2 drho) and dm_n - u drho, the acoustic ones
+// are (dp -+ a (dm_n - u drho)) / (2 a2).
 //
 // TWICE: return 2F instead of F.  Every component of F is half of a sum, and
 // halving is exact, so a caller that scales its use of the flux by 1/2 (the
@@ -184,24 +244,48 @@ __device__ __forceinline__ void hlle(const T L[NV], const T R[NV], T uL, T pL, T
 // without the five multiplications.
 template <typename T, bool TWICE = false>
 __device__ __forceinline__ bool roe(const T L[NV], const T R[NV], const Consts<T> &c, T F[NV]) {
+#pragma clang fp contract(on)
+    constexpr bool F32 = sizeof(T) == 4;
     const T h = c.half;
     const T hf = TWICE ? T(1) : h;  // the flux sums' factor
-    const T qL = rsq(L[0]), qR = rsq(R[0]);
-    const T irL = qL * qL, irR = qR * qR;
+    T irL, irR, qL, qR;  // 1/rho; Roe weights (float: sqrt(rho), double: 1 and sqrt(rho_R / rho_L))
+    if constexpr (F32) {
+        qL = rsq(L[0]);
+        qR = rsq(R[0]);
+        irL = qL * qL;
+        irR = qR * qR;
+    } else {
+        const T x = L[0] * R[0], q = rsq(x), qq = q * q;
+        irL = qq * R[0];
+        irR = qq * L[0];
+        qL = T(1);
+        qR = x * q;
+    }
     const T uL = L[1] * irL, vL = L[2] * irL, wL = L[3] * irL;
     const T uR = R[1] * irR, vR = R[2] * irR, wR = R[3] * irR;
-    const T pL = c.gm1 * (L[4] - h * (L[1] * uL + L[2] * vL + L[3] * wL));
-    const T pR = c.gm1 * (R[4] - h * (R[1] * uR + R[2] * vR + R[3] * wR));
+    const T kL = L[1] * uL, kR = R[1] * uR;
+    const T pL = c.gm1 * (L[4] - h * (kL + L[2] * vL + L[3] * wL));
+    const T pR = c.gm1 * (R[4] - h * (kR + R[2] * vR + R[3] * wR));
     const T c2L = c.g * pL * irL, c2R = c.g * pR * irR;  // squared sound speeds
+    const T eL = L[4] + pL, eR = R[4] + pR;
 
     // Roe averages with weights sqrt(rho): sqrt(rho) u = m / sqrt(rho)
-    const T is = rcp(L[0] * qL + R[0] * qR);
-    const T u = (L[1] * qL + R[1] * qR) * is;
-    const T v = (L[2] * qL + R[2] * qR) * is;
-    const T w = (L[3] * qL + R[3] * qR) * is;
-    const T H = ((L[4] + pL) * qL + (R[4] + pR) * qR) * is;
-    const T q2 = u * u + v * v + w * w;
-    const T a2 = c.gm1 * (H - h * q2);
+    T u, v, w, H;
+    if constexpr (F32) {
+        const T is = rcp(L[0] * qL + R[0] * qR);
+        u = (L[1] * qL + R[1] * qR) * is;
+        v = (L[2] * qL + R[2] * qR) * is;
+        w = (L[3] * qL + R[3] * qR) * is;
+        H = (eL * qL + eR * qR) * is;
+    } else {
+        const T is = rcp(L[0] + qR);
+        u = (L[1] + qR * uR) * is;
+        v = (L[2] + qR * vR) * is;
+        w = (L[3] + qR * wR) * is;
+        H = (eL + qR * (eR * irR)) * is;
+    }
+    const T hq2 = h * (u * u + v * v + w * w);
+    const T a2 = c.gm1 * (H - hq2);
     if (!(a2 > T(0))) {
         hlle(L, R, uL, pL, uR, pR, uL - sqrt_(c2L), uR + sqrt_(c2R), F);
         if (TWICE) {
@@ -214,23 +298,21 @@ __device__ __forceinline__ bool roe(const T L[NV], const T R[NV], const Consts<T
     const T a = a2 * ia;
     const T D0 = R[0] - L[0], D1 = R[1] - L[1], D2 = R[2] - L[2], D3 = R[3] - L[3],
             D4 = R[4] - L[4];
-    const T al3 = D2 - v * D0;
-    const T al4 = D3 - w * D0;
-    const T d5 = D4 - al3 * v - al4 * w;
-    const T al2 = c.gm1 * (ia * ia) * (D0 * (H - u * u) + u * D1 - d5);
-    const T al1 = (D0 * (u + a) - D1 - a * al2) * (h * ia);
-    const T al5 = D0 - (al1 + al2);
-    const T ua = u * a;
+    const T dp = D4 - u * D1 - v * D2 - w * D3 + hq2 * D0;  // over gamma - 1
+    const T X = a * (D1 - u * D0);
+    const T k = h * (ia * ia);
+    const T al1 = (c.gm1 * dp - X) * k, al5 = (c.gm1 * dp + X) * k;
+    const T lam1 = u - a, lam5 = u + a;
 
     // states on the inner sides of the two acoustic waves
-    const T Ls[NV] = {L[0] + al1, L[1] + al1 * (u - a), L[2] + al1 * v, L[3] + al1 * w,
-                      L[4] + al1 * (H - ua)};
-    const T Rs[NV] = {R[0] - al5, R[1] - al5 * (u + a), R[2] - al5 * v, R[3] - al5 * w,
-                      R[4] - al5 * (H + ua)};
-    const T QL = T(2) * Ls[0] * Ls[4] - (Ls[1] * Ls[1] + Ls[2] * Ls[2] + Ls[3] * Ls[3]);
-    const T QR = T(2) * Rs[0] * Rs[4] - (Rs[1] * Rs[1] + Rs[2] * Rs[2] + Rs[3] * Rs[3]);
+    const T Ls[NV] = {L[0] + al1, L[1] + al1 * lam1, L[2] + al1 * v, L[3] + al1 * w,
+                      L[4] + al1 * (H - u * a)};
+    const T Rs[NV] = {R[0] - al5, R[1] - al5 * lam5, R[2] - al5 * v, R[3] - al5 * w,
+                      R[4] - al5 * (H + u * a)};
+    const T QL = (Ls[0] + Ls[0]) * Ls[4] - (Ls[1] * Ls[1] + Ls[2] * Ls[2] + Ls[3] * Ls[3]);
+    const T QR = (Rs[0] + Rs[0]) * Rs[4] - (Rs[1] * Rs[1] + Rs[2] * Rs[2] + Rs[3] * Rs[3]);
     if (!(Ls[0] > T(0) && QL > T(0) && Rs[0] > T(0) && QR > T(0))) {
-        hlle(L, R, uL, pL, uR, pR, fmin(uL - sqrt_(c2L), u - a), fmax(uR + sqrt_(c2R), u + a), F);
+        hlle(L, R, uL, pL, uR, pR, fmin(uL - sqrt_(c2L), lam1), fmax(uR + sqrt_(c2R), lam5), F);
         if (TWICE) {
 #pragma unroll
             for (int m = 0; m < NV; ++m) F[m] *= T(2);
@@ -240,7 +322,6 @@ __device__ __forceinline__ bool roe(const T L[NV], const T R[NV], const Consts<T
     // Harten-Hyman: wave 1 between L (speed uL - cL) and L* (speed (m* - rho* c*)/rho*),
     // wave 5 between R* (speed (m* + rho* c*)/rho*) and R (speed uR + cR).  The fix is
     // active when |lambda| < lambda - lambda_left or |lambda| < lambda_right - lambda.
-    const T lam1 = u - a, lam5 = u + a;
     T ab1 = fabs(lam1), ab5 = fabs(lam5);
     if constexpr (sizeof(T) == 4) {
         const T cL = sqrt_(c2L), cR = sqrt_(c2R);
@@ -278,19 +359,15 @@ __device__ __forceinline__ bool roe(const T L[NV], const T R[NV], const Consts<T
             ab5 = (lam5 * lam5 + e * e) * (h * rcp(e));
         }
     }
-    const T ab2 = fabs(u);
 
-    // dissipation sum_k |lambda_k| alpha_k K_k: waves 1, 2 and 5 share the
-    // transverse components v and w of their eigenvectors, so those rows take
-    // the sum of the three amplitudes once
-    const T c1 = al1 * ab1, c2 = al2 * ab2, c3 = al3 * ab2, c4 = al4 * ab2, c5 = al5 * ab5;
-    const T s125 = (c1 + c2) + c5;
-    F[0] = hf * ((L[1] + R[1]) - s125);
-    F[1] = hf * ((L[1] * uL + pL + R[1] * uR + pR) - ((c1 * (u - a) + c2 * u) + c5 * (u + a)));
-    F[2] = hf * ((L[2] * uL + R[2] * uR) - (s125 * v + c3));
-    F[3] = hf * ((L[3] * uL + R[3] * uR) - (s125 * w + c4));
-    F[4] = hf * (((L[4] + pL) * uL + (R[4] + pR) * uR) -
-                 ((((c1 * (H - ua) + c2 * (h * q2)) + c3 * v) + c4 * w) + c5 * (H + ua)));
+    const T ab2 = fabs(u);
+    const T d5 = ab5 - ab2, e1 = al1 * (ab1 - ab2);
+    const T es = e1 + al5 * d5, et = a * (al5 * d5 - e1);
+    F[0] = hf * (((L[1] + R[1]) - es) - ab2 * D0);
+    F[1] = hf * ((((kL + kR) + (pL + pR)) - et) - es * u - ab2 * D1);
+    F[2] = hf * (L[2] * uL + R[2] * uR - es * v - ab2 * D2);
+    F[3] = hf * (L[3] * uL + R[3] * uR - es * w - ab2 * D3);
+    F[4] = hf * (eL * uL + eR * uR - es * H - et * u - ab2 * D4);
     return false;
 }
 
@@ -310,6 +387,26 @@ __device__ __forceinline__ bool roe_dir(const T UL[NV], const T UR[NV], const Co
     F[4] = Fr[4];
     return fb;
 }
+
+// The arithmetic above as one argument of a kernel (the FP64-state, FP32-arithmetic
+// path takes MixedArith of euler_mixed.h instead).
+template <typename T>
+struct Arith {
+    static __device__ __forceinline__ T limiter(T a, T b, const Consts<T> &c) { return gamer::limiter(a, b, c.k1); }
+    template <int D>
+    static __device__ __forceinline__ void char_slope(const T a[NV], const T b[NV], T h, T q, T cr, T c2,
+                                                      const Consts<T> &c, T dw[NV]) {
+        gamer::char_slope<D>(a, b, h, q, cr, c2, c.k1, dw);
+    }
+    static __device__ __forceinline__ bool predict(const T W0[NV], const T dW[3][NV], T hdt, const Consts<T> &c,
+                                                   T Ub[3][2][NV]) {
+        return gamer::predict(W0, dW, hdt, c, Ub);
+    }
+    // Roe's flux doubled
+    static __device__ __forceinline__ bool roe2(const T L[NV], const T R[NV], const Consts<T> &c, T F[NV]) {
+        return gamer::roe<T, true>(L, R, c, F);
+    }
+};
 
 // Fixed-order reduction of NSTAT doubles per thread over NTHREADS threads
 // (thread index t, 0 .. NTHREADS - 1, NTHREADS a multiple of 64 when the

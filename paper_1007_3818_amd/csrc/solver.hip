@@ -22,9 +22,16 @@
 //    the consumed LDS state.
 //  - Work between two barriers is spread so that no wave carries more than the
 //    heaviest share: in the 256-thread shape the wave that computed the ghost
-//    layer solves its z faces after the x and y faces, while the x faces 16 (on
-//    wave k+1 mod 4) and the y faces 16 (on wave k+2 mod 4) are solved by
-//    other waves, from right states the ghost-layer wave left in LDS.
+//    layer solves its z faces after the x and y faces, while the x and y faces 16
+//    are solved together, 32 lanes in one pass, by another wave (k+2 mod 4), from
+//    right states the ghost-layer wave left in LDS.  (One pass for each of the two
+//    directions, 16 lanes each, cost every wave half a Roe solve per plane.)
+//  - Every register is in use (168 float, three waves per SIMD; 256 double, two),
+//    so addresses of accesses that few steps or few lanes make are formed where
+//    they are used (`fresh`) instead of living across the sweep, and global
+//    accesses take a scalar base and a 32-bit lane offset (`at`).  With the forms
+//    of euler.h this took the double kernel from 9 spilled registers to none and
+//    the 256^3 padded step from 1,070 to 988 us (float: 577 -> 549 us).
 //  - The update of plane k-1 completes at step k, once the z flux above it is
 //    known: U - dt/dh ((dF_x + dF_y) + dF_z), in double for both precisions.
 //  - Plane k+2 is loaded into registers at the top of step k and written to
@@ -40,8 +47,11 @@
 //    counts) are reduced in a fixed order in the epilogue.  An updated cell
 //    that is not physical (rho <= 0, p <= 0) or not finite makes the group's
 //    signal speed NaN and is counted in an optional device counter.
+#include <type_traits>
+
 #include "device_math.h"
 #include "euler.h"
+#include "euler_mixed.h"
 #include "internal.h"
 
 namespace gamer {
@@ -49,12 +59,28 @@ namespace {
 
 constexpr int NINNER = NI * NI;  // 256 interior columns
 
-// Element `off` of a wave-uniform base pointer, for a lane offset known to be
-// non-negative and below 2^32: the access can then take the base in scalar
-// registers and a 32-bit lane offset, with no 64-bit address arithmetic per lane.
-template <typename P>
-__device__ __forceinline__ P &at(P *base, unsigned off) {
-    return base[off];
+// An index taken afresh at this place: what is derived from it (addresses of
+// rarely executed accesses above all) is computed here and not kept in registers
+// across the sweep, where every register is in use.
+__device__ __forceinline__ int fresh(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+// The value at byte offset `off` of a wave-uniform base pointer.  The base is
+// pinned to scalar registers, so that each access takes it as it is: with a 32-bit
+// lane offset (itself taken afresh in the same place) the access needs no vector
+// instruction for its address, with a 64-bit one a single add.  Left alone, the
+// compiler keeps one vector pointer for the five variables and adds their strides
+// to it, two instructions and a wait state per access: 45 of the float sweep's
+// 1,000 vector instructions per wave and plane.
+template <typename P, typename Off>
+__device__ __forceinline__ auto &at(P *base, Off off) {
+    using G = __attribute__((address_space(1))) P;
+    using C = __attribute__((address_space(1))) std::conditional_t<std::is_const_v<P>, const char, char>;
+    C *b = (C *)base;  // global memory, which the pinning would hide
+    asm volatile("" : "+s"(b));
+    return *(G *)(b + off);
 }
 
 template <typename T>
@@ -113,6 +139,22 @@ __device__ __forceinline__ void ring_cell(int r, int &ci, int &cj) {
     }
 }
 
+// Twice Roe's flux along direction D for unrotated conserved states.
+template <int D, class A, typename T>
+__device__ __forceinline__ bool roe2_dir(const T UL[NV], const T UR[NV], const Consts<T> &c, T F[NV]) {
+    constexpr int n = 1 + D, t1 = 1 + (D + 1) % 3, t2 = 1 + (D + 2) % 3;
+    const T L[NV] = {UL[0], UL[n], UL[t1], UL[t2], UL[4]};
+    const T R[NV] = {UR[0], UR[n], UR[t1], UR[t2], UR[4]};
+    T Fr[NV];
+    const bool fb = A::roe2(L, R, c, Fr);
+    F[0] = Fr[0];
+    F[n] = Fr[1];
+    F[t1] = Fr[2];
+    F[t2] = Fr[3];
+    F[4] = Fr[4];
+    return fb;
+}
+
 // Stats values reduced per pass when a group's stats go out in the middle of a
 // unit: the pass's values for every thread must fit in the flux arrays and the
 // face-16 states (sx, sy, rf), the LDS free at that point.
@@ -157,6 +199,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT), amdgpu_waves_per_
 void solve_kernel(SolveParams<S_> P) {
     static_assert(NT == 320 || NT == 256, "work-group shape");
     constexpr bool SPLIT = NT == 320;
+    using A = std::conditional_t<sizeof(S_) == sizeof(T), Arith<T>, MixedArith>;
     __shared__ Lds<T> S;
     const int t = threadIdx.x;
     const int wave = t >> 6;
@@ -268,19 +311,20 @@ void solve_kernel(SolveParams<S_> P) {
         auto fetch = [&](int plane) {  // plane in -2..17
             const S_ *src = plane_base(plane + NG);
             S_ r0[NV], r1[NV];
-            if constexpr (!PERIODIC) {
-#pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    r0[v] = at(src + v * VSTRIDE, unsigned(cp0));
-                    r1[v] = at(src + v * VSTRIDE, unsigned(cp1));
-                }
-            } else {
+            if constexpr (PERIODIC) {
                 const S_ *s0 = src + int64_t(gp0) * GOUT + cp0;
                 const S_ *s1 = src + int64_t(gp1) * GOUT + cp1;
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
                     r0[v] = s0[v * VSTRIDE];
                     r1[v] = s1[v * VSTRIDE];
+                }
+            } else {
+                const unsigned o0 = fresh(cp0 * int(sizeof(S_))), o1 = fresh(cp1 * int(sizeof(S_)));
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    r0[v] = at(src + v * VSTRIDE, o0);
+                    r1[v] = at(src + v * VSTRIDE, o1);
                 }
             }
             // With double storage and float arithmetic the values are narrowed
@@ -400,9 +444,9 @@ void solve_kernel(SolveParams<S_> P) {
                     for (int v = 0; v < NV; ++v) {
                         const T q0 = w0[v][pos];
                         W0[v] = q0;
-                        dW[0][v] = limiter(q0 - w0[v][pos - 1], w0[v][pos + 1] - q0, c.theta);
-                        dW[1][v] = limiter(q0 - w0[v][pos - NP], w0[v][pos + NP] - q0, c.theta);
-                        dW[2][v] = limiter(q0 - wm[v][pos], wq[v][pos] - q0, c.theta);
+                        dW[0][v] = A::limiter(q0 - w0[v][pos - 1], w0[v][pos + 1] - q0, c);
+                        dW[1][v] = A::limiter(q0 - w0[v][pos - NP], w0[v][pos + NP] - q0, c);
+                        dW[2][v] = A::limiter(q0 - wm[v][pos], wq[v][pos] - q0, c);
                     }
                 } else {
 #pragma unroll
@@ -418,23 +462,23 @@ void solve_kernel(SolveParams<S_> P) {
                         a[v] = W0[v] - w0[v][pos - 1];
                         b[v] = w0[v][pos + 1] - W0[v];
                     }
-                    char_slope<0>(a, b, h, q, cr, c2, c.theta, dW[0]);
+                    A::template char_slope<0>(a, b, h, q, cr, c2, c, dW[0]);
 #pragma unroll
                     for (int v = 0; v < NV; ++v) {
                         a[v] = W0[v] - w0[v][pos - NP];
                         b[v] = w0[v][pos + NP] - W0[v];
                     }
-                    char_slope<1>(a, b, h, q, cr, c2, c.theta, dW[1]);
+                    A::template char_slope<1>(a, b, h, q, cr, c2, c, dW[1]);
 #pragma unroll
                     for (int v = 0; v < NV; ++v) {
                         a[v] = W0[v] - wm[v][pos];
                         b[v] = wq[v][pos] - W0[v];
                     }
-                    char_slope<2>(a, b, h, q, cr, c2, c.theta, dW[2]);
+                    A::template char_slope<2>(a, b, h, q, cr, c2, c, dW[2]);
                 }
                 // predicted face states Ubar^{d,+-} = cons(W0 +- dW_d/2) + S
                 T Ub[3][2][NV];
-                if (!predict(W0, dW, T(0.5 * dtdh), c, Ub)) {
+                if (!A::predict(W0, dW, T(0.5 * dtdh), c, Ub)) {
                     // first-order fallback: every face of the cell takes the cell average
                     if constexpr (PERIODIC)
                         step |= round == 0 ? 1 : 2;
@@ -442,7 +486,7 @@ void solve_kernel(SolveParams<S_> P) {
                         ++n_pred;
 #pragma unroll
                     for (int v = 0; v < NV; ++v) {
-                        const T u0 = T(cell_ptr(ci + NG, cj + NG, k + NG)[v * VSTRIDE]);
+                        const T u0 = T(cell_ptr(fresh(ci) + NG, fresh(cj) + NG, k + NG)[v * VSTRIDE]);
 #pragma unroll
                         for (int d = 0; d < 3; ++d) Ub[d][0][v] = Ub[d][1][v] = u0;
                     }
@@ -492,13 +536,13 @@ void solve_kernel(SolveParams<S_> P) {
             T fzn[NV];
             auto solve_z = [&]() {
                 if (inner && k >= 0) {
-                    const bool fb = roe_dir<2, true>(zp, zm, c, fzn);
+                    const bool fb = roe2_dir<2, A>(zp, zm, c, fzn);
                     if constexpr (PERIODIC)
                         step |= int(fb) << 2;
                     else if (!SUB || k < nplanes || last)
                         n_roe += fb;
                     if (P.flux) {
-                        const int off = jj * NI + ii;
+                        const int off = fresh(jj * NI + ii);
                         if constexpr (PERIODIC) {
                             // face kl of group gk (below the unit's last plane), and face 16
                             // of the group below when the face lies on a group boundary
@@ -524,75 +568,71 @@ void solve_kernel(SolveParams<S_> P) {
             if (!late_z) solve_z();
             __syncthreads();  // B2: +x / +y states and the right states of faces 16 visible
 
-            // faces 16: x by wave k+1 mod 4 and y by wave k+2 mod 4 (320 threads:
-            // both by the ghost-layer wave), lanes 0..15
-            const int lane = t & 63;
-            const bool x16 = lane < NI && (SPLIT ? wave == 4 : wave == ((k + 1) & 3));
-            const bool y16 = lane < NI && (SPLIT ? wave == 4 : wave == ((k + 2) & 3));
-
             if (!edge) {
-                // x faces: face ci of each interior cell, then face 16 of each row
+                if (inner) {
+                    // x face ii, then y face jj, of this thread's cell
+                    T UL[NV], F[NV];
 #pragma unroll
-                for (int round = 0; round < 2; ++round) {
-                    int row, f;
-                    if (round == 0) {
-                        if (!inner) continue;
-                        row = jj;
-                        f = ii;
-                    } else {
-                        if (!x16) continue;
-                        row = lane;
-                        f = NI;
-                    }
-                    T UL[NV], UR[NV], F[NV];
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) {
-                        UL[v] = S.sx[v][row][f];
-                        UR[v] = round == 0 ? xm[v] : S.rf[0][v][row];
-                    }
-                    const bool fb = roe_dir<0, true>(UL, UR, c, F);
+                    for (int v = 0; v < NV; ++v) UL[v] = S.sx[v][jj][ii];
+                    bool fb = roe2_dir<0, A>(UL, xm, c, F);
                     if constexpr (PERIODIC)
                         step += int(fb) << 3;
                     else
                         n_roe += fb;
 #pragma unroll
-                    for (int v = 0; v < NV; ++v) S.sx[v][row][f] = F[v];
-                    if (P.flux && (f & 7) == 0) {
-                        S_ *dst = P.flux + gk * GFLX + ((0 * 3 + (f >> 3)) * NV) * NINNER + kl * NI + row;
+                    for (int v = 0; v < NV; ++v) S.sx[v][jj][ii] = F[v];
+                    if (P.flux && (ii & 7) == 0) {
+                        S_ *dst = P.flux + gk * GFLX + ((0 * 3 + (fresh(ii) >> 3)) * NV) * NINNER + kl * NI + fresh(jj);
+#pragma unroll
+                        for (int v = 0; v < NV; ++v) dst[v * NINNER] = S_(c.half * F[v]);
+                    }
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) UL[v] = S.sy[v][jj][ii];
+                    fb = roe2_dir<1, A>(UL, ym, c, F);
+                    if constexpr (PERIODIC)
+                        step += int(fb) << 3;
+                    else
+                        n_roe += fb;
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) S.sy[v][jj][ii] = F[v];
+                    if (P.flux && (jj & 7) == 0) {
+                        S_ *dst = P.flux + gk * GFLX + ((1 * 3 + (fresh(jj) >> 3)) * NV) * NINNER + kl * NI + fresh(ii);
 #pragma unroll
                         for (int v = 0; v < NV; ++v) dst[v * NINNER] = S_(c.half * F[v]);
                     }
                 }
-                // y faces: face cj of each interior cell, then face 16 of each column
-#pragma unroll
-                for (int round = 0; round < 2; ++round) {
-                    int col, f;
-                    if (round == 0) {
-                        if (!inner) continue;
-                        col = ii;
-                        f = jj;
-                    } else {
-                        if (!y16) continue;
-                        col = lane;
-                        f = NI;
-                    }
-                    T UL[NV], UR[NV], F[NV];
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) {
-                        UL[v] = S.sy[v][f][col];
-                        UR[v] = round == 0 ? ym[v] : S.rf[1][v][col];
-                    }
-                    const bool fb = roe_dir<1, true>(UL, UR, c, F);
+                // The faces 16, one solve for both directions: lanes 0..15 of wave
+                // k+2 mod 4 (320 threads: the ghost-layer wave) take the x faces of
+                // rows 0..15, lanes 16..31 the y faces of columns 0..15.  The two
+                // arrays have the same stride per variable, so a lane's direction is
+                // only a base and the order it reads the momenta in.
+                const int lane = fresh(t & 63);
+                if (lane < 2 * NI && (SPLIT ? wave == 4 : wave == ((k + 2) & 3))) {
+                    constexpr int FSTR = NI * (NI + 1);
+                    const int q = lane & (NI - 1), y = lane >> 4;
+                    T *l = y ? &S.sy[0][NI][q] : &S.sx[0][q][NI];
+                    const T *r = &S.rf[y][0][q];
+                    const int cn = y ? 2 : 1, c1 = y ? 3 : 2, c2 = y ? 1 : 3;  // normal, transverse
+                    const T UL[NV] = {l[0], l[cn * FSTR], l[c1 * FSTR], l[c2 * FSTR], l[4 * FSTR]};
+                    const T UR[NV] = {r[0], r[cn * NI], r[c1 * NI], r[c2 * NI], r[4 * NI]};
+                    T F[NV];
+                    const bool fb = A::roe2(UL, UR, c, F);
                     if constexpr (PERIODIC)
                         step += int(fb) << 3;
                     else
                         n_roe += fb;
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) S.sy[v][f][col] = F[v];
-                    if (P.flux && (f & 7) == 0) {
-                        S_ *dst = P.flux + gk * GFLX + ((1 * 3 + (f >> 3)) * NV) * NINNER + kl * NI + col;
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) dst[v * NINNER] = S_(c.half * F[v]);
+                    l[0] = F[0];
+                    l[cn * FSTR] = F[1];
+                    l[c1 * FSTR] = F[2];
+                    l[c2 * FSTR] = F[3];
+                    l[4 * FSTR] = F[4];
+                    if (P.flux) {
+                        S_ *dst = P.flux + gk * GFLX + ((y * 3 + 2) * NV) * NINNER + kl * NI + q;
+                        dst[0] = S_(c.half * F[0]);
+                        dst[cn * NINNER] = S_(c.half * F[1]);
+                        dst[c1 * NINNER] = S_(c.half * F[2]);
+                        dst[c2 * NINNER] = S_(c.half * F[3]);
+                        dst[4 * NINNER] = S_(c.half * F[4]);
                     }
                 }
             }
@@ -611,7 +651,7 @@ void solve_kernel(SolveParams<S_> P) {
                 // an interior cell: in the group's own block in both input kinds
                 const S_ *src = PERIODIC ? P.in + gu * GOUT + ul * NINNER
                                          : P.in + g * GIN + (zg(k - 1) + NG) * NPL + NG * NP + NG;
-                const unsigned off = PERIODIC ? unsigned(t) : unsigned(jj * NP + ii);
+                const unsigned off = fresh(int((PERIODIC ? unsigned(t) : unsigned(jj * NP + ii)) * sizeof(S_)));
 #pragma unroll
                 for (int v = 0; v < NV; ++v) uold[v] = at(src + v * VSTRIDE, off);
             };
@@ -625,12 +665,13 @@ void solve_kernel(SolveParams<S_> P) {
                     S_ *dst = P.out + gu * GOUT + ul * NINNER;
                     if (!EARLY) load_old();
                     T un[NV];
+                    const unsigned ob = fresh(int(t * sizeof(S_)));
 #pragma unroll
                     for (int v = 0; v < NV; ++v) {
                         const double dfz = double(fzn[v]) - double(fz[v]);
                         const double r = double(uold[v]) - hdtdh * (S.dxy[v][t] + dfz);
                         const S_ o = S_(r);
-                        at(dst + v * NI * NINNER, unsigned(t)) = o;
+                        at(dst + v * NI * NINNER, ob) = o;
                         un[v] = T(o);
                         st[v] += double(o);
                     }
