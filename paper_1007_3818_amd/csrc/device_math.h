@@ -1,7 +1,9 @@
-// device_math.h -- arithmetic helpers shared by the solver and the stats kernels.
+// device_math.h -- arithmetic and addressing helpers shared by the kernels.
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 namespace gamer {
 
@@ -68,6 +70,30 @@ template <typename T>
 __device__ __forceinline__ Consts<T> make_consts(double gamma, double theta) {
     return Consts<T>{T(gamma), T(gamma - 1.0), T(1.0 / (gamma - 1.0)), T(theta), T(0.5), T(0.5 * theta), T(0.5 / theta),
                      T(0.5 * gamma * (gamma - 1.0))};
+}
+
+// An index taken afresh at this place: what is derived from it (addresses of
+// rarely executed accesses above all) is computed here and not kept in registers
+// across the sweep, where every register is in use.
+__device__ __forceinline__ int fresh(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+// The value at byte offset `off` of a wave-uniform base pointer.  The base is
+// pinned to scalar registers, so that each access takes it as it is: with a 32-bit
+// lane offset (itself taken afresh in the same place) the access needs no vector
+// instruction for its address, with a 64-bit one a single add.  Left alone, the
+// compiler keeps one vector pointer for the five variables and adds their strides
+// to it, two instructions and a wait state per access: 45 of the float sweep's
+// 1,000 vector instructions per wave and plane.
+template <typename P, typename Off>
+__device__ __forceinline__ auto &at(P *base, Off off) {
+    using G = __attribute__((address_space(1))) P;
+    using C = __attribute__((address_space(1))) std::conditional_t<std::is_const_v<P>, const char, char>;
+    C *b = (C *)base;  // global memory, which the pinning would hide
+    asm volatile("" : "+s"(b));
+    return *(G *)(b + off);
 }
 
 }  // namespace gamer

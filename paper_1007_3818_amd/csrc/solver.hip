@@ -47,8 +47,6 @@
 //    counts) are reduced in a fixed order in the epilogue.  An updated cell
 //    that is not physical (rho <= 0, p <= 0) or not finite makes the group's
 //    signal speed NaN and is counted in an optional device counter.
-#include <type_traits>
-
 #include "device_math.h"
 #include "euler.h"
 #include "euler_mixed.h"
@@ -58,30 +56,6 @@ namespace gamer {
 namespace {
 
 constexpr int NINNER = NI * NI;  // 256 interior columns
-
-// An index taken afresh at this place: what is derived from it (addresses of
-// rarely executed accesses above all) is computed here and not kept in registers
-// across the sweep, where every register is in use.
-__device__ __forceinline__ int fresh(int x) {
-    asm volatile("" : "+v"(x));
-    return x;
-}
-
-// The value at byte offset `off` of a wave-uniform base pointer.  The base is
-// pinned to scalar registers, so that each access takes it as it is: with a 32-bit
-// lane offset (itself taken afresh in the same place) the access needs no vector
-// instruction for its address, with a 64-bit one a single add.  Left alone, the
-// compiler keeps one vector pointer for the five variables and adds their strides
-// to it, two instructions and a wait state per access: 45 of the float sweep's
-// 1,000 vector instructions per wave and plane.
-template <typename P, typename Off>
-__device__ __forceinline__ auto &at(P *base, Off off) {
-    using G = __attribute__((address_space(1))) P;
-    using C = __attribute__((address_space(1))) std::conditional_t<std::is_const_v<P>, const char, char>;
-    C *b = (C *)base;  // global memory, which the pinning would hide
-    asm volatile("" : "+s"(b));
-    return *(G *)(b + off);
-}
 
 template <typename T>
 struct alignas(16) Lds {
