@@ -153,68 +153,79 @@ __global__ __launch_bounds__(256) void group_stats_kernel(const T *__restrict__ 
 }
 
 // ---- fixed-order reduction of group stats ----------------------------------
-// One work-group of RT threads.  Thread t folds groups t, t+RT, ... in order;
-// each wave combines its lanes by a fixed shuffle tree and wave 0 combines the
-// waves in order.  The result does not depend on timing.  Maxima keep NaN, so
-// a level holding a non-physical cell gets a NaN time step.
+// One work-group of RT threads.  Each thread folds its groups in order, each wave
+// its lanes by a fixed shuffle tree, and one thread per value the waves in order;
+// the result does not depend on timing.  Maxima keep NaN, so a level holding a
+// non-physical cell gets a NaN time step.
+//
+// One level (a uniform grid): thread t takes pair r = t mod 4 (stats 2r, 2r + 1) of
+// groups t / 4, t / 4 + RT / 4, ..., so that a wave reads 1 KiB of consecutive stats
+// per load.  Several levels: a thread takes whole groups t, t + RT, ..., since the
+// weights and maxima by level would cost the pairs' four threads each.  Bound by the
+// one CU that reads them: 262,144 groups of one level 259 -> 154 us, 24,608 29 -> 14
+// (of three levels 31 -> 30); the kernel alone takes 4 us for a few groups, 12 us with
+// one thread folding the waves of every value.
 constexpr int RT = 1024;
 constexpr int RW = RT / 64;
-constexpr int RU = 4;  // groups per thread whose loads are in flight together
-constexpr int RL = 4;  // levels whose maxima are taken in the totals' pass
+constexpr int RP1 = 8;  // groups per thread whose loads are in flight together, one level
+constexpr int RU = 4;   // and several levels
+constexpr int RL = 4;   // levels whose maxima are taken in the totals' pass
 
-template <int N>
-__device__ void block_fold(double (&x)[N], const bool (&is_max)[N], double (*red)[RW]) {
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-#pragma unroll
-        for (int q = 0; q < N; ++q) {
-            const double y = __shfl_down(x[q], off, 64);
-            x[q] = is_max[q] ? max_nan(x[q], y) : x[q] + y;
-        }
-    }
-    if (lane == 0) {
-#pragma unroll
-        for (int q = 0; q < N; ++q) red[q][wave] = x[q];
-    }
-    __syncthreads();
-    if (t == 0) {
-#pragma unroll
-        for (int q = 0; q < N; ++q) {
-            double a = red[q][0];
-            for (int w = 1; w < RW; ++w) a = is_max[q] ? max_nan(a, red[q][w]) : a + red[q][w];
-            x[q] = a;
-        }
-    }
-    __syncthreads();
-}
+struct alignas(8) StatPair {  // read as one 16-byte load; the array is 8-byte aligned
+    double a, b;
+};
 
+template <bool ONE>  // ONE: n_levels is 1 and level is null
 __global__ __launch_bounds__(RT) void reduce_kernel(const double *__restrict__ stats, int64_t n,
                                                     const int8_t *__restrict__ level,
                                                     const double *__restrict__ dh_dev, double dh,
                                                     int n_levels, double cfl,
                                                     double *__restrict__ dt_out,
                                                     double *__restrict__ totals_out) {
-    // values folded: [0..4] dh^3-weighted sums of stats 0..4, [5..6] sums of
-    // stats 6..7, [7..7+RL) the signal-speed maxima of levels 0..RL-1
-    __shared__ double red[7 + RL][RW];
-    const int t = threadIdx.x;
-    // one pass over the stats for the totals and, up to RL levels, the maxima;
-    // more levels take one further pass per level for their maxima
-    const bool tot = totals_out != nullptr;
-    const int lv_one = dt_out ? (n_levels <= RL ? n_levels : 0) : 0;
-    double x[7 + RL];
-    bool is_max[7 + RL];
+    // sums of stats 0..7, 0..4 weighted by dh^3 ([5] not used), then the signal-speed
+    // maxima of levels 0..RL-1
+    constexpr int NR = NSTAT + RL;
+    __shared__ double red[NR][RW];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int folded = n_levels <= RL ? n_levels : 0;  // levels whose maxima are taken here
+    if constexpr (ONE) {
+        const int r = t & 3;
+        const StatPair *pairs = reinterpret_cast<const StatPair *>(stats) + r;
+        const double h = dh_dev ? dh_dev[0] : dh;
+        const double w = r == 3 ? 1.0 : h * h * h;
+        double a = 0.0, b = 0.0, m = 0.0;
+        auto fold = [&](const StatPair &p) {
+            a += w * p.a;
+            b += w * p.b;
+            m = max_nan(m, p.b);  // stat 5 where r is 2
+        };
+        int64_t g = t >> 2;
+        for (; g + int64_t(RT / 4) * (RP1 - 1) < n; g += int64_t(RT / 4) * RP1) {
+            StatPair s[RP1];
 #pragma unroll
-    for (int q = 0; q < 7 + RL; ++q) {
-        x[q] = 0.0;
-        is_max[q] = q >= 7;
-    }
-    // RU groups' loads are issued before any is folded (a pass over 10^5
-    // groups is otherwise one memory latency per group per thread); each
-    // thread folds its groups in the order t, t + RT, t + 2 RT, ...
-    if (tot || lv_one > 0) {
-        for (int64_t g0 = t; g0 < n; g0 += int64_t(RT) * RU) {
+            for (int u = 0; u < RP1; ++u) s[u] = pairs[(g + int64_t(u) * (RT / 4)) * (NSTAT / 2)];
+            __builtin_amdgcn_sched_barrier(0);  // every load issued before the first is used
+#pragma unroll
+            for (int u = 0; u < RP1; ++u) fold(s[u]);
+        }
+        for (; g < n; g += RT / 4) fold(pairs[g * (NSTAT / 2)]);
+#pragma unroll
+        for (int off = 32; off >= 4; off >>= 1) {
+            a += __shfl_down(a, off, 64);
+            b += __shfl_down(b, off, 64);
+            m = max_nan(m, __shfl_down(m, off, 64));
+        }
+        if (lane < 4) {
+            red[2 * r][wave] = a;
+            red[2 * r + 1][wave] = b;
+            if (r == 2) red[NSTAT][wave] = m;
+        }
+    } else {
+        double x[NR];
+#pragma unroll
+        for (int q = 0; q < NR; ++q) x[q] = 0.0;
+        const int64_t end = totals_out || folded > 0 ? n : 0;  // nothing to take in this pass
+        for (int64_t g0 = t; g0 < end; g0 += int64_t(RT) * RU) {
             double s[RU][NSTAT], w[RU];
             int lv[RU];
             bool ok[RU];
@@ -237,52 +248,59 @@ __global__ __launch_bounds__(RT) void reduce_kernel(const double *__restrict__ s
 #pragma unroll
             for (int u = 0; u < RU; ++u) {
                 if (!ok[u]) continue;
-                if (tot) {
 #pragma unroll
-                    for (int q = 0; q < 5; ++q) x[q] += w[u] * s[u][q];
-                    x[5] += s[u][6];
-                    x[6] += s[u][7];
-                }
+                for (int q = 0; q < NSTAT; ++q)
+                    if (q != 5) x[q] += q < 5 ? w[u] * s[u][q] : s[u][q];
 #pragma unroll
                 for (int L = 0; L < RL; ++L)
-                    if (L < lv_one && lv[u] == L) x[7 + L] = max_nan(x[7 + L], s[u][5]);
+                    if (L < folded && lv[u] == L) x[NSTAT + L] = max_nan(x[NSTAT + L], s[u][5]);
             }
         }
-        block_fold(x, is_max, red);
-        if (t == 0) {
-            if (tot) {
 #pragma unroll
-                for (int q = 0; q < 7; ++q) totals_out[q] = x[q];
+        for (int off = 32; off >= 1; off >>= 1) {
+#pragma unroll
+            for (int q = 0; q < NR; ++q) {
+                const double y = __shfl_down(x[q], off, 64);
+                x[q] = q >= NSTAT ? max_nan(x[q], y) : x[q] + y;
             }
+        }
+        if (lane == 0) {
+#pragma unroll
+            for (int q = 0; q < NR; ++q) red[q][wave] = x[q];
         }
     }
-    if (dt_out) {
-        const bool max1[1] = {true};
+    __syncthreads();
+    auto write_dt = [&](int L, double top) {
+        const double hL = dh_dev ? dh_dev[L] : dh;
+        // NaN when a group of the level has a non-physical cell
+        dt_out[L] = top > 0.0 ? cfl * hL / top : (top != top ? top : INFINITY);
+    };
+    if (t < NSTAT + folded) {
+        double x = red[t][0];
+        for (int w = 1; w < RW; ++w) x = t < NSTAT ? x + red[t][w] : max_nan(x, red[t][w]);
+        if (t < NSTAT) {
+            if (totals_out && t != 5) totals_out[t < 5 ? t : t - 1] = x;
+        } else if (dt_out) {
+            write_dt(t - NSTAT, x);
+        }
+    }
+    // more levels: one pass over the stats for the maximum of each
+    if (dt_out && n_levels > RL) {
         for (int L = 0; L < n_levels; ++L) {
-            double m[1] = {0.0};
-            if (L < lv_one) {
-                m[0] = x[7 + (L < RL ? L : 0)];  // thread 0 holds the folded value
-            } else {
-                for (int64_t g0 = t; g0 < n; g0 += int64_t(RT) * RU) {
-                    double sp[RU];
-                    bool take[RU];
-#pragma unroll
-                    for (int u = 0; u < RU; ++u) {
-                        const int64_t g1 = g0 + int64_t(u) * RT;
-                        const int64_t g = g1 < n ? g1 : g0;
-                        take[u] = g1 < n && (level ? int(level[g]) : 0) == L;
-                        sp[u] = stats[g * NSTAT + 5];
-                    }
-#pragma unroll
-                    for (int u = 0; u < RU; ++u)
-                        if (take[u]) m[0] = max_nan(m[0], sp[u]);
-                }
-                block_fold(m, max1, red);
+            double x = 0.0;
+#pragma unroll 4
+            for (int64_t g = t; g < n; g += RT) {
+                const double sp = stats[g * NSTAT + 5];
+                if ((level ? int(level[g]) : 0) == L) x = max_nan(x, sp);
             }
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) x = max_nan(x, __shfl_down(x, off, 64));
+            __syncthreads();  // the last values read from red[0]
+            if (lane == 0) red[0][wave] = x;
+            __syncthreads();
             if (t == 0) {
-                const double hL = dh_dev ? dh_dev[L] : dh;
-                // NaN when a group of the level has a non-physical cell
-                dt_out[L] = m[0] > 0.0 ? cfl * hL / m[0] : (m[0] != m[0] ? m[0] : INFINITY);
+                for (int w = 1; w < RW; ++w) x = max_nan(x, red[0][w]);
+                write_dt(L, x);
             }
         }
     }
@@ -313,8 +331,8 @@ hipError_t launch_group_stats(const T *groups, int64_t n, double gamma, double *
 hipError_t launch_reduce(const double *stats, int64_t n, const int8_t *level, const double *dh_dev,
                          double dh, int n_levels, double cfl, double *dt_out, double *totals_out,
                          hipStream_t s) {
-    hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(RT), 0, s, stats, n, level, dh_dev, dh,
-                       n_levels, cfl, dt_out, totals_out);
+    const auto kernel = n_levels == 1 && !level ? reduce_kernel<true> : reduce_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(RT), 0, s, stats, n, level, dh_dev, dh, n_levels, cfl, dt_out, totals_out);
     return hipGetLastError();
 }
 
