@@ -6,7 +6,7 @@
 // ctu_fused (variant 0, the default): 384 threads per group sweeping z with
 // every intermediate on chip (two groups side by side per work-group in
 // float, so that the work-group's 12 waves sit three to a SIMD).  Thread
-// t < 324 of a group owns the column (i, j) of the 18 x 18 square of cells
+// t < 324 of a group owns a column of the 18 x 18 square of cells
 // -1..16; step s (planes s = -1..16):
 //   A  the z predictor of plane s, the transverse z flux between planes s - 1
 //      and s (registers: this thread holds the plus-z state below), the
@@ -14,10 +14,19 @@
 //      one below it, both in registers, and plane s - 1's transverse x and y
 //      fluxes from LDS), then the x and y predictor of plane s;
 //   C  (after a barrier) the transverse x and y fluxes of plane s and the final
-//      x and y fluxes of plane s - 1, into LDS;
+//      x and y fluxes of plane s - 1, into LDS, and the primitive states of padded plane s + 2 into the ring, in the
+//      place of plane s - 1, which A was the last to read;
 //   E  (after a barrier) the corrected z states of plane s, the final z flux
-//      between planes s - 1 and s, the update of plane s - 1 and the primitive
-//      states of padded plane s + 2 into the ring.
+//      between planes s - 1 and s and the update of plane s - 1.
+// E and the next step's A need no barrier between them: E reads the flux arrays
+// of C and A writes the state arrays.  The inner columns are threads 0..255 of a
+// group, the square's four edges one wave and its corners another: only the
+// first four waves take part in E, which the edges' and corners' waves pass by
+// on their way to the next A.  With columns numbered row by row (six waves in
+// every phase, a third of E's lanes idle) and the plane stored after E, behind a
+// third barrier, a step of 256^3 took 1.480 ms in float and 3.553 ms in double,
+// against 1.384 and 3.056 ms; a SIMD has at most three waves in float and two in
+// double to hide a barrier with.
 // Nothing is written to memory but the result, the flux planes and the stats.
 //
 // The pipeline (variant 1) keeps its intermediate arrays in a caller-provided
@@ -454,7 +463,8 @@ struct FusedLds {
     };
 };
 
-// Threads per group: one per cell of an 18 x 18 plane (324 of 384 busy).
+// Threads per group: one per cell of an 18 x 18 plane (324 of 384 busy: four waves
+// of inner columns, one of edges, one with the corners).
 // LDS per group: 70 KB in float, 140 KB in double.  A work-group sweeps
 // FusedShape::groups groups side by side, so that its waves spread evenly over
 // the CU's four SIMDs (a lone 6-wave work-group puts two waves on two SIMDs
@@ -527,7 +537,18 @@ void ctu_fused(CtuArgs<T> P) {
     const int t = threadIdx.x - half * NT;
     if (live && !lev_ok && P.bad && t == 0) atomicAdd(P.bad + 1, 1ull);
     const bool mine = live && t < CE * CE;
-    const int i = t % CE - 1, j = t / CE - 1;  // this thread's column, meaningful when mine
+    // this thread's column, meaningful when mine: the 16 x 16 inner columns in order,
+    // then the four edges of the 18 x 18 square, then its corners
+    const int e = t - NINNER;
+    int i = t & 15, j = t >> 4;
+    if (e >= 0) {
+        i = e >= 32 ? (e & 15) : (e & 16 ? NI : -1);
+        j = e >= 32 ? (e & 16 ? NI : -1) : (e & 15);
+    }
+    if (e >= 64) {
+        i = e & 1 ? NI : -1;
+        j = e & 2 ? NI : -1;
+    }
     const int ii = i + NG, jj = j + NG;        // its padded position
     const bool in_i = i >= 0 && i < NI, in_j = j >= 0 && j < NI;
     int n_pred = 0, n_roe = 0;
@@ -557,9 +578,11 @@ void ctu_fused(CtuArgs<T> P) {
     };
     // The sweep's next plane: in float its conserved values are loaded into
     // registers at the top of a step (positions t and t + NT of the 20 x 20
-    // plane) and converted into the ring at the step's end, so the loads overlap
+    // plane) and converted into the ring at the end of C, so the loads overlap
     // the step (2.17 -> 2.04 ms at 256^3).  In double those registers spill
-    // (3.39 -> 4.39 ms), and the plane is loaded and converted at the step's end.
+    // (3.39 -> 4.39 ms), and the plane is loaded and converted at the end of C.
+    // (One wave filling the plane in C for all waits out the loads: float 1.384 ->
+    // 1.47 ms, double at 9^3 groups 598 -> 697 us.)
     constexpr bool PREFETCH = sizeof(T) == 4;
     constexpr int NPOS = (NPL + NT - 1) / NT;
     T pre[NPOS][NV];
@@ -600,11 +623,11 @@ void ctu_fused(CtuArgs<T> P) {
     fill(-2);
     fill(-1);
     fill(0);
+    __syncthreads();
 
     for (int s = -1; s <= NI; ++s) {
         const bool ahead = s + 2 <= NI + 1;
         if (PREFETCH && ahead) fetch(s + 2);
-        __syncthreads();  // B0: padded planes s - 1, s, s + 1 in the ring
         const int sm = (s + 2) % 3, s0 = (s + 3) % 3, sp = (s + 4) % 3;
         const bool e1 = mine && in_e1(i, j, s);
         const int kb = s - 1;  // the plane whose x / y states are corrected and fluxes finished
@@ -748,6 +771,12 @@ void ctu_fused(CtuArgs<T> P) {
                 }
             }
         }
+        if (ahead) {  // into the slot of plane s - 1, which A was the last to read
+            if constexpr (PREFETCH)
+                store(s + 2);
+            else
+                fill(s + 2);
+        }
         __syncthreads();  // B2: transverse fluxes of plane s, final x / y fluxes of plane kb
 
         // ---- E: corrected z states of plane s, final z flux below it, update of plane kb
@@ -794,12 +823,6 @@ void ctu_fused(CtuArgs<T> P) {
         for (int v = 0; v < NV; ++v) {
             zpp[v] = zpn[v];
             ftzb[v] = ftz[v];
-        }
-        if (ahead) {  // into the slot of plane s - 1, no longer read
-            if constexpr (PREFETCH)
-                store(s + 2);
-            else
-                fill(s + 2);
         }
     }
     if (P.bad && n_bad) atomicAdd(P.bad, (unsigned long long)n_bad);
