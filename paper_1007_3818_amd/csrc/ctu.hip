@@ -14,8 +14,9 @@
 //      one below it, both in registers, and plane s - 1's transverse x and y
 //      fluxes from LDS), then the x and y predictor of plane s;
 //   C  (after a barrier) the transverse x and y fluxes of plane s and the final
-//      x and y fluxes of plane s - 1, into LDS, and the primitive states of padded plane s + 2 into the ring, in the
-//      place of plane s - 1, which A was the last to read;
+//      x and y fluxes of plane s - 1, into LDS, and the primitive states of
+//      padded plane s + 2 into the ring, in the place of plane s - 1, which A was
+//      the last to read;
 //   E  (after a barrier) the corrected z states of plane s, the final z flux
 //      between planes s - 1 and s and the update of plane s - 1.
 // E and the next step's A need no barrier between them: E reads the flux arrays
@@ -549,8 +550,19 @@ void ctu_fused(CtuArgs<T> P) {
         i = e & 1 ? NI : -1;
         j = e & 2 ? NI : -1;
     }
-    const int ii = i + NG, jj = j + NG;        // its padded position
-    const bool in_i = i >= 0 && i < NI, in_j = j >= 0 && j < NI;
+    int ii = i + NG, jj = j + NG;              // its padded position
+    bool in_i = i >= 0 && i < NI, in_j = j >= 0 && j < NI;
+    // The column taken afresh: in double, addresses and conditions formed before
+    // are not kept in registers past this place (256 and 52 bytes of scratch ->
+    // 240 and none).  In float, where they fit, it costs more than it frees.
+    constexpr bool F64 = sizeof(T) == 8;
+    auto afresh = [&]() {
+        if constexpr (F64) {
+            i = fresh(i), j = fresh(j);
+            ii = i + NG, jj = j + NG;
+            in_i = i >= 0 && i < NI, in_j = j >= 0 && j < NI;
+        }
+    };
     int n_pred = 0, n_roe = 0;
     unsigned n_bad = 0;
     double st[NSTAT];
@@ -576,41 +588,46 @@ void ctu_fused(CtuArgs<T> P) {
             for (int v = 0; v < NV; ++v) S.a.w[slot][v][qj][qi] = w[v];
         }
     };
-    // The sweep's next plane: in float its conserved values are loaded into
-    // registers at the top of a step (positions t and t + NT of the 20 x 20
-    // plane) and converted into the ring at the end of C, so the loads overlap
-    // the step (2.17 -> 2.04 ms at 256^3).  In double those registers spill
-    // (3.39 -> 4.39 ms), and the plane is loaded and converted at the end of C.
-    // (One wave filling the plane in C for all waits out the loads: float 1.384 ->
-    // 1.47 ms, double at 9^3 groups 598 -> 697 us.)
-    constexpr bool PREFETCH = sizeof(T) == 4;
-    constexpr int NPOS = (NPL + NT - 1) / NT;
+    // The sweep's next plane is loaded ahead and converted into the ring at the end
+    // of C.  In float, positions t and t + NT of the 20 x 20 plane are loaded at the
+    // top of a step (2.17 -> 2.04 ms at 256^3).  In double those registers spill;
+    // position t is loaded at the top of C, and the 16 positions past NT by the
+    // corners' wave, which is the first to end C (9^3 groups 581 -> 556 us against
+    // loading the plane at the end of C).  One wave filling the plane in C for all
+    // waits out the loads: float 1.384 -> 1.472 ms, double 598 -> 697 us.
+    constexpr int NPOS = F64 ? 1 : (NPL + NT - 1) / NT;
     T pre[NPOS][NV];
+    auto load = [&](int m, int q, T u[NV]) {
+        const T *src = U + (m + NG) * NPL + q;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) u[v] = src[v * NP * NP * NP];
+    };
+    auto to_ring = [&](int m, int q, const T p[NV]) {
+        const T ir = rcp(p[0]);
+        const T u = p[1] * ir, v = p[2] * ir, wz = p[3] * ir;
+        T *dst = &S.a.w[(m + 3) % 3][0][0][0] + q;
+        dst[0 * NPL] = p[0];
+        dst[1 * NPL] = u;
+        dst[2 * NPL] = v;
+        dst[3 * NPL] = wz;
+        dst[4 * NPL] = c.gm1 * (p[4] - c.half * p[0] * (u * u + v * v + wz * wz));
+    };
     auto fetch = [&](int m) {
 #pragma unroll
-        for (int r = 0; r < NPOS; ++r) {
-            const int q = t + r * NT;
-            if (q < NPL) {
-                const T *src = U + (m + NG) * NPL + q;
-#pragma unroll
-                for (int v = 0; v < NV; ++v) pre[r][v] = src[v * NP * NP * NP];
-            }
-        }
+        for (int r = 0; r < NPOS; ++r)
+            if (t + r * NT < NPL) load(m, t + r * NT, pre[r]);
     };
     auto store = [&](int m) {
-        const int slot = (m + 3) % 3;
 #pragma unroll
-        for (int r = 0; r < NPOS; ++r) {
-            const int q = t + r * NT;
-            if (q < NPL) {
-                const T ir = rcp(pre[r][0]);
-                const T u = pre[r][1] * ir, v = pre[r][2] * ir, wz = pre[r][3] * ir;
-                T *dst = &S.a.w[slot][0][0][0] + q;
-                dst[0 * NPL] = pre[r][0];
-                dst[1 * NPL] = u;
-                dst[2 * NPL] = v;
-                dst[3 * NPL] = wz;
-                dst[4 * NPL] = c.gm1 * (pre[r][4] - c.half * pre[r][0] * (u * u + v * v + wz * wz));
+        for (int r = 0; r < NPOS; ++r)
+            if (t + r * NT < NPL) to_ring(m, t + r * NT, pre[r]);
+        if constexpr (F64) {
+            static_assert(NT <= NPL && NPL - NT <= 64, "one more position for some lanes of the last wave");
+            const int q = t + 64;
+            if (q >= NT && q < NPL) {
+                T u[NV];
+                load(m, q, u);
+                to_ring(m, q, u);
             }
         }
     };
@@ -627,7 +644,7 @@ void ctu_fused(CtuArgs<T> P) {
 
     for (int s = -1; s <= NI; ++s) {
         const bool ahead = s + 2 <= NI + 1;
-        if (PREFETCH && ahead) fetch(s + 2);
+        if (!F64 && ahead) fetch(s + 2);
         const int sm = (s + 2) % 3, s0 = (s + 3) % 3, sp = (s + 4) % 3;
         const bool e1 = mine && in_e1(i, j, s);
         const int kb = s - 1;  // the plane whose x / y states are corrected and fluxes finished
@@ -652,6 +669,7 @@ void ctu_fused(CtuArgs<T> P) {
             }
             if (s >= 0 && in_e1(i, j, s - 1)) n_roe += roe_dir<2, true>(zpp, zm, c, ftz);
         }
+        afresh();
         // corrected x and y states of plane kb (whose other two coordinates lie in
         // the interior); the plus states go to LDS for the neighbour's face
         T cxm[NV], cym[NV];
@@ -726,6 +744,8 @@ void ctu_fused(CtuArgs<T> P) {
             for (int v = 0; v < NV; ++v) uold[v] = U[v * (NP * NP * NP) + ((kb + NG) * NP + jj) * NP + ii];
         }
 
+        if (F64 && ahead) fetch(s + 2);
+
         // ---- C: transverse x / y fluxes of plane s, final x / y fluxes of plane kb
         if (e1) {
             T R[NV], F[NV];
@@ -746,7 +766,38 @@ void ctu_fused(CtuArgs<T> P) {
         }
         if (mine && kb >= 0 && kb < NI) {
             T L[NV], F[NV];
-            if (in_j && i >= 0) {  // x face i of row j: plus-x of cell i - 1, minus-x of cell i
+            if (F64 && t >= NINNER) {
+                // In double, where registers allow, the faces 16 of both directions in
+                // one solve: a lane's direction is only a base and the order it takes
+                // the momenta in (9^3 groups 597 -> 581 us; float spills, 1.384 -> 1.393 ms).
+                const bool y = j == NI;
+                if (y ? in_i : i == NI && in_j) {
+                    constexpr int FSTR = NI * (NI + 1);
+                    const int q = y ? i : j, o = y ? NI * NI + q : q * (NI + 1) + NI;
+                    const int cn = y ? 2 : 1, c1 = y ? 3 : 2, c2 = y ? 1 : 3;  // normal, transverse
+                    const T *l = (y ? &S.a.cyp[0][0][0] : &S.a.cxp[0][0][0]) + o;
+                    T *f = (y ? &S.a.fy[0][0][0] : &S.a.fx[0][0][0]) + o;
+                    const T UL[NV] = {l[0], l[cn * FSTR], l[c1 * FSTR], l[c2 * FSTR], l[4 * FSTR]};
+                    const T UR[NV] = {y ? cym[0] : cxm[0], y ? cym[2] : cxm[1], y ? cym[3] : cxm[2],
+                                      y ? cym[1] : cxm[3], y ? cym[4] : cxm[4]};
+                    n_roe += roe<T, true>(UL, UR, c, F);
+                    f[0] = F[0];
+                    f[cn * FSTR] = F[1];
+                    f[c1 * FSTR] = F[2];
+                    f[c2 * FSTR] = F[3];
+                    f[4 * FSTR] = F[4];
+                    if (P.flux) {
+                        T *dst = P.flux + g * GFLX + ((y * 3 + 2) * NV) * NINNER + kb * NI + q;
+                        dst[0] = c.half * F[0];
+                        dst[cn * NINNER] = c.half * F[1];
+                        dst[c1 * NINNER] = c.half * F[2];
+                        dst[c2 * NINNER] = c.half * F[3];
+                        dst[4 * NINNER] = c.half * F[4];
+                    }
+                }
+            }
+            // x face i of row j: plus-x of cell i - 1, minus-x of cell i
+            if (F64 ? t < NINNER : in_j && i >= 0) {
 #pragma unroll
                 for (int v = 0; v < NV; ++v) L[v] = S.a.cxp[v][j][i];
                 n_roe += roe_dir<0, true>(L, cxm, c, F);
@@ -758,7 +809,7 @@ void ctu_fused(CtuArgs<T> P) {
                     for (int v = 0; v < NV; ++v) dst[v * NINNER] = c.half * F[v];
                 }
             }
-            if (in_i && j >= 0) {  // y face j of column i
+            if (F64 ? t < NINNER : in_i && j >= 0) {  // y face j of column i
 #pragma unroll
                 for (int v = 0; v < NV; ++v) L[v] = S.a.cyp[v][j][i];
                 n_roe += roe_dir<1, true>(L, cym, c, F);
@@ -771,14 +822,10 @@ void ctu_fused(CtuArgs<T> P) {
                 }
             }
         }
-        if (ahead) {  // into the slot of plane s - 1, which A was the last to read
-            if constexpr (PREFETCH)
-                store(s + 2);
-            else
-                fill(s + 2);
-        }
+        if (ahead) store(s + 2);  // into the slot of plane s - 1, which A was the last to read
         __syncthreads();  // B2: transverse fluxes of plane s, final x / y fluxes of plane kb
 
+        afresh();
         // ---- E: corrected z states of plane s, final z flux below it, update of plane kb
         if (mine && in_i && in_j) {
             T a[NV], b[NV], czm[NV], fz[NV];
