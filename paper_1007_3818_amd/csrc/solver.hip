@@ -349,6 +349,15 @@ void solve_kernel(SolveParams<S_> P) {
                 to_lds(slot, has1 ? p1 : p0, q1[pl]);
             }
         }
+        // Where the barrier between two steps stands.  In float it comes as soon as a
+        // step's fluxes are read, with the next plane already stored before B3 (its
+        // slot is free from B2 on), so that the update and the next step's predictor
+        // run as one phase: 256^3 padded 546 -> 537 us, periodic 600 -> 590.  With
+        // double storage the sums it holds across the barrier spill: double 1,042 ->
+        // 1,122, mixed 13 x 11 x 9 groups 288 -> 292; there the barrier is B1, and the
+        // plane is stored after B3.
+        constexpr bool MERGE = sizeof(S_) == 4 && !SPLIT;
+        if (MERGE) __syncthreads();
 
         // carried across sweep steps
         T zp[NV];            // +z state of this column at the previous plane
@@ -375,10 +384,11 @@ void solve_kernel(SolveParams<S_> P) {
         }
 
         // Plane k+2 is fetched into registers at the top of step k and written
-        // to the ring after B3, into the slot of plane k-1, which step k no
+        // to the ring next to B3, into the slot of plane k-1, which step k no
         // longer reads by then.  Consuming it there, before the update's stores
         // are issued, keeps the wait for the loads from also waiting out those
-        // stores (memory operations complete in issue order).
+        // stores (memory operations complete in issue order; with MERGE the stores
+        // before the loads are a whole step old).
         for (int k = -1; k <= nplanes; ++k) {
             // plane k of the unit is plane kl of its group gk (k in 0 .. nplanes-1;
             // with padded input, the group itself)
@@ -386,7 +396,7 @@ void solve_kernel(SolveParams<S_> P) {
             const int64_t gk = PERIODIC ? g + int64_t(kq) * cols : g;
             const bool ahead = k + 2 <= nplanes + 1;
             if (ahead) fetch(k + 2);
-            __syncthreads();  // B1: plane k+1 visible; planes k-1, k, k+1 in the ring
+            if (!MERGE) __syncthreads();  // B1: plane k+1 visible; planes k-1, k, k+1 in the ring
 
             const bool edge = (k < 0 || k >= nplanes);
             if constexpr (PERIODIC) step = 0;
@@ -629,10 +639,27 @@ void solve_kernel(SolveParams<S_> P) {
 #pragma unroll
                 for (int v = 0; v < NV; ++v) uold[v] = at(src + v * VSTRIDE, off);
             };
+            if (MERGE && ahead) store(k + 2);
             if (EARLY && inner && k >= 1) load_old();
             __syncthreads();  // B3: x / y fluxes visible; plane k-1 no longer read
-            if (ahead) store(k + 2);
+            if (!MERGE && ahead) store(k + 2);
 
+            auto new_dxy = [&](int v) {
+                return (double(S.sx[v][jj][ii + 1]) - double(S.sx[v][jj][ii])) +
+                       (double(S.sy[v][jj + 1][ii]) - double(S.sy[v][jj][ii]));
+            };
+            double dold[NV];
+            if constexpr (MERGE) {
+                if (inner) {
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) dold[v] = S.dxy[v][t];
+                    if (!edge) {
+#pragma unroll
+                        for (int v = 0; v < NV; ++v) S.dxy[v][t] = new_dxy(v);
+                    }
+                }
+                __syncthreads();  // the fluxes are read; the next step may write its states there
+            }
             if (inner) {
                 if (k >= 1) {
                     // plane k-1 is complete: U - dt/dh ((dF_x + dF_y) + dF_z)
@@ -643,7 +670,7 @@ void solve_kernel(SolveParams<S_> P) {
 #pragma unroll
                     for (int v = 0; v < NV; ++v) {
                         const double dfz = double(fzn[v]) - double(fz[v]);
-                        const double r = double(uold[v]) - hdtdh * (S.dxy[v][t] + dfz);
+                        const double r = double(uold[v]) - hdtdh * ((MERGE ? dold[v] : S.dxy[v][t]) + dfz);
                         const S_ o = S_(r);
                         at(dst + v * NI * NINNER, ob) = o;
                         un[v] = T(o);
@@ -653,11 +680,9 @@ void solve_kernel(SolveParams<S_> P) {
                     n_bad += sp != sp;
                     st[5] = max_nan(st[5], sp);
                 }
-                if (!edge) {
+                if (!MERGE && !edge) {
 #pragma unroll
-                    for (int v = 0; v < NV; ++v)
-                        S.dxy[v][t] = (double(S.sx[v][jj][ii + 1]) - double(S.sx[v][jj][ii])) +
-                                      (double(S.sy[v][jj + 1][ii]) - double(S.sy[v][jj][ii]));
+                    for (int v = 0; v < NV; ++v) S.dxy[v][t] = new_dxy(v);
                 }
                 if (k >= 0) {
 #pragma unroll
