@@ -880,9 +880,6 @@ namespace {
 // 216 groups FP32 101 -> 74 in 2 (77 in 4); 512 groups FP32 116 -> 125 in 2.
 template <typename T>
 int choose_parts(int64_t n) {
-#ifdef FORCE_NSUB
-    return FORCE_NSUB;
-#endif
     constexpr int64_t slots = 256 * (sizeof(T) == 4 ? 3 : 2);
     for (int s = MAX_PARTS; s > 1; s /= 2)
         if (n * s <= slots) return s;
