@@ -75,7 +75,7 @@ GAMMA = 5.0 / 3.0
 CFL = 0.5
 
 
-SOLVER_SOURCES = ("solver.hip", "euler.h", "device_math.h", "internal.h")
+SOLVER_SOURCES = ("solver.hip", "euler.h", "euler_mixed.h", "device_math.h", "internal.h")
 
 
 def read_profile_values(name):
@@ -201,8 +201,8 @@ def bench_dtype(tag, state, g, dh, steps, warmup, workload, shape=None, pick=Non
         # a plain copy's counters; None unless taken on these sources and shape
         "traffic": read_traffic(tag, variant, grid, n_groups),
         # the instantiation as rocprofv3 names it: <storage, arithmetic, threads,
-        # waves per SIMD, periodic input, characteristic limiting>
-        "kernel": "solve_kernel<{0}, {0}, {1}, {2}, false, false>".format(
+        # waves per SIMD, periodic input, characteristic limiting, groups in parts>
+        "kernel": "solve_kernel<{0}, {0}, {1}, {2}, false, false, false>".format(
             "float" if tag == "f32" else "double", *hydro.solver_variants(padded.dtype)[variant]),
         "kernel_ms": k_ms,
         "kernel_ms_median": k_median,
