@@ -173,6 +173,9 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT), amdgpu_waves_per_
 void solve_kernel(SolveParams<S_> P) {
     static_assert(NT == 320 || NT == 256, "work-group shape");
     constexpr bool SPLIT = NT == 320;
+    // float at four waves per SIMD, 128 registers: what is loaded ahead or indexed twice
+    // spills (256^3 padded 1,111 -> 953 us without, periodic 1,338 -> 1,081)
+    constexpr bool TIGHT = sizeof(S_) == 4 && WAVES >= 4;
     using A = std::conditional_t<sizeof(S_) == sizeof(T), Arith<T>, MixedArith>;
     __shared__ Lds<T> S;
     const int t = threadIdx.x;
@@ -273,7 +276,7 @@ void solve_kernel(SolveParams<S_> P) {
         // interior reads contiguous rows of the group itself (1024^3: 35.5 ->
         // 35.0 ms).  With double storage the extra registers of that order spill
         // (15 -> 22) and cost more than it saves; it keeps the row order.
-        constexpr bool INTERIOR_FIRST = PERIODIC && sizeof(S_) == 4;
+        constexpr bool INTERIOR_FIRST = PERIODIC && sizeof(S_) == 4 && !TIGHT;
         const bool has1 = t + NT < NPL;
         const int p0 = INTERIOR_FIRST ? plane_pos(t) : t;
         const int p1 = INTERIOR_FIRST ? (has1 ? plane_pos(t + NT) : p0) : t + NT;
@@ -626,7 +629,7 @@ void solve_kernel(SolveParams<S_> P) {
             // the arrays distinct, and would otherwise wait out a store before
             // each load).  With float arithmetic, where registers allow, the loads
             // are issued before the barrier, so their latency overlaps the wait.
-            constexpr bool EARLY = sizeof(T) == 4;
+            constexpr bool EARLY = sizeof(T) == 4 && !TIGHT;
             S_ uold[NV];
             // plane k-1 of the unit: plane ul of group gu
             const int ul = PERIODIC ? zg(k - 1) & 15 : zg(k - 1);
