@@ -360,12 +360,16 @@ __device__ __forceinline__ bool roe(const T L[NV], const T R[NV], const Consts<T
             const T lr = lam * rs;
             const T e = fmax((lam - (us - s1)) * rs, (ms - s2) - lr);  // the larger gap, times rho*
             const T ab = (lr * lr + e * e) * (h * rcp(e * rs));
-            ab1 = fix1 ? ab : ab1;
-            ab5 = fix1 ? ab5 : ab;
+            // The gap has to exceed |lambda| itself: the squares above may pass a face
+            // whose gap comes out as |lambda| or less, down to zero at a uniform flow
+            // of exactly the speed of sound (where the quotient would be 0 / 0).
+            const bool wide = e > fabs(lr);
+            ab1 = fix1 && wide ? ab : ab1;
+            ab5 = !fix1 && wide ? ab : ab5;
             if (fix1 && fix5) {
                 const T l5 = lam5 * Rs[0];
                 const T e5 = fmax(((uR + sqrt_(c2R)) - lam5) * Rs[0], l5 - (Rs[1] + sqrt_(c.gq * QR)));
-                ab5 = (l5 * l5 + e5 * e5) * (h * rcp(e5 * Rs[0]));
+                if (e5 > fabs(l5)) ab5 = (l5 * l5 + e5 * e5) * (h * rcp(e5 * Rs[0]));
             }
         }
     }
