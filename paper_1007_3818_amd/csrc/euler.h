@@ -221,13 +221,13 @@ __device__ __forceinline__ void hlle(const T L[NV], const T R[NV], T uL, T pL, T
 // Roe flux between rotated conserved states (component 1 = normal momentum).
 // Harten-Hyman entropy fix on the acoustic waves, HLLE when a2 <= 0 or an
 // intermediate state is unphysical.  Returns true when HLLE was used.
-// Arithmetic layout: in float one reciprocal square root per side gives
-// sqrt(rho) and 1/rho; in double, where it takes five more instructions and
-// sixteen cycles, one of the product rho_L rho_R gives both 1/rho and the Roe
-// weight sqrt(rho_L rho_R).  One of a2 gives a and 1/a; the intermediate states' positivity and
-// rho c come from Q = 2 rho E - |m|^2 (p > 0 <=> Q > 0, (rho c)^2 = gq Q), so
-// they need no reciprocal unless the entropy fix is active on that lane.  In
-// double, where a square root is a refined estimate of about fifteen
+// Arithmetic layout: one reciprocal square root per side gives sqrt(rho) and 1/rho
+// (one of the product rho_L rho_R would give both sides' with an instruction or two
+// less, but leaves the double range at densities of 1e-154 and 1e154, and gives two
+// negative densities a root); one of a2 gives a and 1/a; the intermediate states'
+// positivity and rho c come from Q = 2 rho E - |m|^2 (p > 0 <=> Q > 0, (rho c)^2 =
+// gq Q), so they need no reciprocal unless the entropy fix is active on that lane.
+// In double, where a square root is a refined estimate of about fifteen
 // instructions, the entropy fix is tested on squared speeds (c^2 = gamma p /
 // rho, (rho* c*)^2 = gq Q*), and the square roots are taken only on lanes where
 // the fix is active or HLLE is used; in float the square root is one hardware
@@ -245,22 +245,10 @@ __device__ __forceinline__ void hlle(const T L[NV], const T R[NV], T uL, T pL, T
 template <typename T, bool TWICE = false>
 __device__ __forceinline__ bool roe(const T L[NV], const T R[NV], const Consts<T> &c, T F[NV]) {
 #pragma clang fp contract(on)
-    constexpr bool F32 = sizeof(T) == 4;
     const T h = c.half;
     const T hf = TWICE ? T(1) : h;  // the flux sums' factor
-    T irL, irR, qL, qR;  // 1/rho; Roe weights (float: sqrt(rho), double: 1 and sqrt(rho_R / rho_L))
-    if constexpr (F32) {
-        qL = rsq(L[0]);
-        qR = rsq(R[0]);
-        irL = qL * qL;
-        irR = qR * qR;
-    } else {
-        const T x = L[0] * R[0], q = rsq(x), qq = q * q;
-        irL = qq * R[0];
-        irR = qq * L[0];
-        qL = T(1);
-        qR = x * q;
-    }
+    const T qL = rsq(L[0]), qR = rsq(R[0]);
+    const T irL = qL * qL, irR = qR * qR;
     const T uL = L[1] * irL, vL = L[2] * irL, wL = L[3] * irL;
     const T uR = R[1] * irR, vR = R[2] * irR, wR = R[3] * irR;
     const T kL = L[1] * uL, kR = R[1] * uR;
@@ -270,20 +258,11 @@ __device__ __forceinline__ bool roe(const T L[NV], const T R[NV], const Consts<T
     const T eL = L[4] + pL, eR = R[4] + pR;
 
     // Roe averages with weights sqrt(rho): sqrt(rho) u = m / sqrt(rho)
-    T u, v, w, H;
-    if constexpr (F32) {
-        const T is = rcp(L[0] * qL + R[0] * qR);
-        u = (L[1] * qL + R[1] * qR) * is;
-        v = (L[2] * qL + R[2] * qR) * is;
-        w = (L[3] * qL + R[3] * qR) * is;
-        H = (eL * qL + eR * qR) * is;
-    } else {
-        const T is = rcp(L[0] + qR);
-        u = (L[1] + qR * uR) * is;
-        v = (L[2] + qR * vR) * is;
-        w = (L[3] + qR * wR) * is;
-        H = (eL + qR * (eR * irR)) * is;
-    }
+    const T is = rcp(L[0] * qL + R[0] * qR);
+    const T u = (L[1] * qL + R[1] * qR) * is;
+    const T v = (L[2] * qL + R[2] * qR) * is;
+    const T w = (L[3] * qL + R[3] * qR) * is;
+    const T H = (eL * qL + eR * qR) * is;
     const T hq2 = h * (u * u + v * v + w * w);
     const T a2 = c.gm1 * (H - hq2);
     if (!(a2 > T(0))) {
@@ -348,8 +327,9 @@ __device__ __forceinline__ bool roe(const T L[NV], const T R[NV], const Consts<T
         const T A5 = ab5 + (lam5 - uR), B5 = (lam5 - ab5) * Rs[0] - Rs[1];
         const bool fix1 = A1 < T(0) || c2L > A1 * A1 || (B1 > T(0) && c.gq * QL < B1 * B1);
         const bool fix5 = A5 < T(0) || c2R > A5 * A5 || (B5 > T(0) && c.gq * QR < B5 * B5);
-        // Faces with either fix take its two square roots and one reciprocal
-        // together, wave 5 as the mirror image of wave 1; hardly any face has both.
+        // Faces with either fix take its two square roots and two reciprocals (one
+        // of rho*^2 e would do, over half the range) together, wave 5 as the mirror
+        // image of wave 1; hardly any face has both.
         // In a flow of strong contrasts a seventh of the faces has one of them, so
         // that most waves hold both kinds: 1,009 groups with flux planes 338 ->
         // 329 us, and fewer registers (256^3 periodic, smooth, 1,055 -> 1,037 us).
@@ -357,19 +337,17 @@ __device__ __forceinline__ bool roe(const T L[NV], const T R[NV], const Consts<T
             const T s1 = sqrt_(fix1 ? c2L : c2R), s2 = sqrt_(c.gq * (fix1 ? QL : QR));
             const T lam = fix1 ? lam1 : -lam5, us = fix1 ? uL : -uR;
             const T ms = fix1 ? Ls[1] : -Rs[1], rs = fix1 ? Ls[0] : Rs[0];
-            const T lr = lam * rs;
-            const T e = fmax((lam - (us - s1)) * rs, (ms - s2) - lr);  // the larger gap, times rho*
-            const T ab = (lr * lr + e * e) * (h * rcp(e * rs));
+            const T e = fmax(lam - (us - s1), ((ms - s2) - lam * rs) * rcp(rs));  // the larger gap
+            const T ab = (lam * lam + e * e) * (h * rcp(e));
             // The gap has to exceed |lambda| itself: the squares above may pass a face
             // whose gap comes out as |lambda| or less, down to zero at a uniform flow
             // of exactly the speed of sound (where the quotient would be 0 / 0).
-            const bool wide = e > fabs(lr);
+            const bool wide = e > fabs(lam);
             ab1 = fix1 && wide ? ab : ab1;
             ab5 = !fix1 && wide ? ab : ab5;
             if (fix1 && fix5) {
-                const T l5 = lam5 * Rs[0];
-                const T e5 = fmax(((uR + sqrt_(c2R)) - lam5) * Rs[0], l5 - (Rs[1] + sqrt_(c.gq * QR)));
-                if (e5 > fabs(l5)) ab5 = (l5 * l5 + e5 * e5) * (h * rcp(e5 * Rs[0]));
+                const T e5 = fmax((uR + sqrt_(c2R)) - lam5, (lam5 * Rs[0] - (Rs[1] + sqrt_(c.gq * QR))) * rcp(Rs[0]));
+                if (e5 > fabs(lam5)) ab5 = (lam5 * lam5 + e5 * e5) * (h * rcp(e5));
             }
         }
     }
