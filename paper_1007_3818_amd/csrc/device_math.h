@@ -75,7 +75,8 @@ __device__ __forceinline__ Consts<T> make_consts(double gamma, double theta) {
 // An index taken afresh at this place: what is derived from it (addresses of
 // rarely executed accesses above all) is computed here and not kept in registers
 // across the sweep, where every register is in use.
-__device__ __forceinline__ int fresh(int x) {
+template <typename T>
+__device__ __forceinline__ T fresh(T x) {
     asm volatile("" : "+v"(x));
     return x;
 }

@@ -109,7 +109,9 @@ __device__ __forceinline__ void cons_prim(const T w[NV], const Consts<T> &c, T u
 // and their flux difference taken into the increment,
 //   S += F_D(minus) - F_D(plus),
 // product by product: every term but the pressure's is one multiply-add (the
-// pressure's is -dp of the slope), against a flux formed, subtracted and added.
+// pressure's is -dp of the slope), against a flux formed, subtracted and added.  The
+// energy's larger product, the internal energy at Mach numbers below one, is the one
+// that goes unrounded into the multiply-add (float: 6% off the mass flux's error).
 template <typename T>
 struct FacePair {
     T rho[2], u[2][3], mn[2], e[2];
@@ -125,7 +127,7 @@ __device__ __forceinline__ void face_pair(const T W0[NV], const T dw[NV], const 
         for (int v = 0; v < NV; ++v) w[v] = side ? W0[v] + c.ht * dw[v] : W0[v] - c.ht * dw[v];
         const T r = w[0], p = w[4], un = w[1 + D];
         const T mn = r * un;
-        const T e = (c.half * r) * (w[1] * w[1] + w[2] * w[2] + w[3] * w[3]) + p * c.igm1;
+        const T e = p * c.igm1 + (c.half * r) * (w[1] * w[1] + w[2] * w[2] + w[3] * w[3]);
         f.rho[side] = r;
         f.mn[side] = mn;
         f.e[side] = e;
@@ -237,6 +239,11 @@ __device__ __forceinline__ void hlle(const T L[NV], const T R[NV], T uL, T pL, T
 // acoustic waves: the three waves of speed u then need no strengths, and with
 // dp = (gamma-1)(dE - u.dm + |u|^2/2 drho) and dm_n - u drho, the acoustic ones
 // are (dp -+ a (dm_n - u drho)) / (2 a2).
+// Rounding: what the dissipation and the pressures are made of is added up before it
+// meets the far larger sums of the two physical fluxes, one rounding at their size.
+// Subtracted from them term by term, the momentum fluxes' error grew by a fifth in
+// smooth flow (rms against 64-bit significands, both types; as here 0.97 to 1.01 of
+// the plain form's, which subtracts the fluxes of two formed wave sums).
 //
 // TWICE: return 2F instead of F.  Every component of F is half of a sum, and
 // halving is exact, so a caller that scales its use of the flux by 1/2 (the
@@ -252,8 +259,13 @@ __device__ __forceinline__ bool roe(const T L[NV], const T R[NV], const Consts<T
     const T uL = L[1] * irL, vL = L[2] * irL, wL = L[3] * irL;
     const T uR = R[1] * irR, vR = R[2] * irR, wR = R[3] * irR;
     const T kL = L[1] * uL, kR = R[1] * uR;
-    const T pL = c.gm1 * (L[4] - h * (kL + L[2] * vL + L[3] * wL));
-    const T pR = c.gm1 * (R[4] - h * (kR + R[2] * vR + R[3] * wR));
+    const T iL = L[4] - h * (kL + L[2] * vL + L[3] * wL);  // internal energies
+    const T iR = R[4] - h * (kR + R[2] * vR + R[3] * wR);
+    const T pL = c.gm1 * iL, pR = c.gm1 * iR;
+    // HLLE's pressures: in float formed again there, so that only the internal energies
+    // stay in registers for the flux sums (256^3 periodic 603 -> 595 us; in double the
+    // other way round, CTU 9 x 8 x 7 groups 376 -> 364 us)
+    auto hlle_p = [&](T i, T p) { return sizeof(T) == 4 ? c.gm1 * fresh(i) : p; };
     const T c2L = c.g * pL * irL, c2R = c.g * pR * irR;  // squared sound speeds
     const T eL = L[4] + pL, eR = R[4] + pR;
 
@@ -266,7 +278,7 @@ __device__ __forceinline__ bool roe(const T L[NV], const T R[NV], const Consts<T
     const T hq2 = h * (u * u + v * v + w * w);
     const T a2 = c.gm1 * (H - hq2);
     if (!(a2 > T(0))) {
-        hlle(L, R, uL, pL, uR, pR, uL - sqrt_(c2L), uR + sqrt_(c2R), F);
+        hlle(L, R, uL, hlle_p(iL, pL), uR, hlle_p(iR, pR), uL - sqrt_(c2L), uR + sqrt_(c2R), F);
         if (TWICE) {
 #pragma unroll
             for (int m = 0; m < NV; ++m) F[m] *= T(2);
@@ -291,7 +303,7 @@ __device__ __forceinline__ bool roe(const T L[NV], const T R[NV], const Consts<T
     const T QL = (Ls[0] + Ls[0]) * Ls[4] - (Ls[1] * Ls[1] + Ls[2] * Ls[2] + Ls[3] * Ls[3]);
     const T QR = (Rs[0] + Rs[0]) * Rs[4] - (Rs[1] * Rs[1] + Rs[2] * Rs[2] + Rs[3] * Rs[3]);
     if (!(Ls[0] > T(0) && QL > T(0) && Rs[0] > T(0) && QR > T(0))) {
-        hlle(L, R, uL, pL, uR, pR, fmin(uL - sqrt_(c2L), lam1), fmax(uR + sqrt_(c2R), lam5), F);
+        hlle(L, R, uL, hlle_p(iL, pL), uR, hlle_p(iR, pR), fmin(uL - sqrt_(c2L), lam1), fmax(uR + sqrt_(c2R), lam5), F);
         if (TWICE) {
 #pragma unroll
             for (int m = 0; m < NV; ++m) F[m] *= T(2);
@@ -355,11 +367,11 @@ __device__ __forceinline__ bool roe(const T L[NV], const T R[NV], const Consts<T
     const T ab2 = fabs(u);
     const T d5 = ab5 - ab2, e1 = al1 * (ab1 - ab2);
     const T es = e1 + al5 * d5, et = a * (al5 * d5 - e1);
-    F[0] = hf * (((L[1] + R[1]) - es) - ab2 * D0);
-    F[1] = hf * ((((kL + kR) + (pL + pR)) - et) - es * u - ab2 * D1);
-    F[2] = hf * (L[2] * uL + R[2] * uR - es * v - ab2 * D2);
-    F[3] = hf * (L[3] * uL + R[3] * uR - es * w - ab2 * D3);
-    F[4] = hf * (eL * uL + eR * uR - es * H - et * u - ab2 * D4);
+    F[0] = hf * ((L[1] + R[1]) - (es + ab2 * D0));
+    F[1] = hf * (((kL + c.gm1 * iL) + (kR + c.gm1 * iR)) - (et + es * u + ab2 * D1));
+    F[2] = hf * ((L[2] * uL + R[2] * uR) - (es * v + ab2 * D2));
+    F[3] = hf * ((L[3] * uL + R[3] * uR) - (es * w + ab2 * D3));
+    F[4] = hf * ((eL * uL + eR * uR) - (es * H + et * u + ab2 * D4));
     return false;
 }
 
