@@ -58,10 +58,7 @@ __device__ __forceinline__ Step<T> make_step(const SweepArgs<T> &P, int64_t g) {
 }
 
 // The right- and left-moving fluxes r = c u + F_D(u) and l = c u - F_D(u), with the
-// freezing speed c = |v_D| + c_s.  F is v_D u plus the pressure terms, so r and l
-// are u times c + v_D = c_s + 2 max(v_D, 0) and c - v_D = c_s + 2 max(-v_D, 0),
-// plus and minus those terms: 27 operations where forming c u and F first takes
-// 37, and no cancellation in c - |v_D|.
+// freezing speed c = |v_D| + c_s: ten multiply-adds on the five fluxes.
 template <int D, typename T>
 __device__ __forceinline__ void relax(const T u[NV], const Step<T> &c, T r[NV], T l[NV]) {
 #pragma clang fp contract(on)
@@ -69,13 +66,16 @@ __device__ __forceinline__ void relax(const T u[NV], const Step<T> &c, T r[NV], 
     const T vx = u[1] * ir, vy = u[2] * ir, vz = u[3] * ir;
     const T vd = D == 0 ? vx : (D == 1 ? vy : vz);
     const T p = c.gm1 * (u[4] - T(0.5) * (u[1] * vx + u[2] * vy + u[3] * vz));
-    const T cs = sqrt_(c.g * p * ir);
-    const T ap = cs + T(2) * fmax(vd, T(0)), am = cs + T(2) * fmax(-vd, T(0));
-    const T pv = p * vd;
+    const T s = fabs(vd) + sqrt_(c.g * p * ir);
+    T F[NV];
+#pragma unroll
+    for (int v = 1; v < 4; ++v) F[v] = v == 1 + D ? u[v] * vd + p : u[v] * vd;
+    F[0] = u[1 + D];
+    F[4] = (u[4] + p) * vd;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        r[v] = v == 1 + D ? u[v] * ap + p : (v == 4 ? u[v] * ap + pv : u[v] * ap);
-        l[v] = v == 1 + D ? u[v] * am - p : (v == 4 ? u[v] * am - pv : u[v] * am);
+        r[v] = s * u[v] + F[v];
+        l[v] = s * u[v] - F[v];
     }
 }
 
