@@ -153,8 +153,8 @@ __global__ __launch_bounds__(256) void group_stats_kernel(const T *__restrict__ 
 }
 
 // ---- fixed-order reduction of group stats ----------------------------------
-// One work-group of RT threads.  Each thread folds its groups in order, each wave
-// its lanes by a fixed shuffle tree, and one thread per value the waves in order;
+// One work-group of RT threads.  Each thread folds its groups in a fixed order, each
+// wave its lanes by a fixed shuffle tree, and one thread per value the waves in order;
 // the result does not depend on timing.  Maxima keep NaN, so a level holding a
 // non-physical cell gets a NaN time step.
 //
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(256) void group_stats_kernel(const T *__restrict__ 
 // groups t / 4, t / 4 + RT / 4, ..., so that a wave reads 1 KiB of consecutive stats
 // per load.  Several levels: a thread takes whole groups t, t + RT, ..., since the
 // weights and maxima by level would cost the pairs' four threads each.  Bound by the
-// one CU that reads them: 262,144 groups of one level 259 -> 154 us, 24,608 29 -> 14
+// one CU that reads them: 262,144 groups of one level 259 -> 159 us, 24,608 29 -> 15
 // (of three levels 31 -> 30); the kernel alone takes 4 us for a few groups, 12 us with
 // one thread folding the waves of every value.
 constexpr int RT = 1024;
@@ -194,21 +194,38 @@ __global__ __launch_bounds__(RT) void reduce_kernel(const double *__restrict__ s
         const double h = dh_dev ? dh_dev[0] : dh;
         const double w = r == 3 ? 1.0 : h * h * h;
         double a = 0.0, b = 0.0, m = 0.0;
-        auto fold = [&](const StatPair &p) {
-            a += w * p.a;
-            b += w * p.b;
-            m = max_nan(m, p.b);  // stat 5 where r is 2
-        };
         int64_t g = t >> 2;
-        for (; g + int64_t(RT / 4) * (RP1 - 1) < n; g += int64_t(RT / 4) * RP1) {
+        // RP1 groups at once, summed pair by pair: with RT / 4 threads per value, adding
+        // them one by one would put four times as many roundings in a row as a thread
+        // per group does, and this puts no more of them for any n
+        auto fold = [&](auto whole) {
             StatPair s[RP1];
+            bool ok[RP1];
 #pragma unroll
-            for (int u = 0; u < RP1; ++u) s[u] = pairs[(g + int64_t(u) * (RT / 4)) * (NSTAT / 2)];
+            for (int u = 0; u < RP1; ++u) {
+                const int64_t gu = g + int64_t(u) * (RT / 4);
+                ok[u] = decltype(whole)::value || gu < n;
+                s[u] = pairs[(ok[u] ? gu : g) * (NSTAT / 2)];
+            }
             __builtin_amdgcn_sched_barrier(0);  // every load issued before the first is used
 #pragma unroll
-            for (int u = 0; u < RP1; ++u) fold(s[u]);
-        }
-        for (; g < n; g += RT / 4) fold(pairs[g * (NSTAT / 2)]);
+            for (int u = 0; u < RP1; ++u) {
+                if (!ok[u]) s[u] = StatPair{0.0, 0.0};
+                m = max_nan(m, s[u].b);  // stat 5 where r is 2
+            }
+#pragma unroll
+            for (int d = 1; d < RP1; d *= 2) {
+#pragma unroll
+                for (int u = 0; u < RP1; u += 2 * d) {
+                    s[u].a += s[u + d].a;
+                    s[u].b += s[u + d].b;
+                }
+            }
+            a += w * s[0].a;
+            b += w * s[0].b;
+        };
+        for (; g + int64_t(RT / 4) * (RP1 - 1) < n; g += int64_t(RT / 4) * RP1) fold(std::true_type());
+        if (g < n) fold(std::false_type());
 #pragma unroll
         for (int off = 32; off >= 4; off >>= 1) {
             a += __shfl_down(a, off, 64);
