@@ -51,10 +51,11 @@ __device__ __forceinline__ double sqrt_(double x) {
 // when the state is not physical (rho <= 0 or p <= 0) or not finite: such a
 // state has no sound speed, and the NaN carries through the maxima below to
 // the time step instead of being dropped.  The solver epilogue and the
-// stand-alone stats kernel both use this function, so their per-group maxima
-// agree bitwise.
+// stand-alone stats kernel both use this function, whose multiply-adds contract
+// within one expression only, so their per-group maxima agree bitwise.
 template <typename T>
 __device__ __forceinline__ T signal_speed(T r, T mx, T my, T mz, T e, const Consts<T> &c) {
+#pragma clang fp contract(on)
     const T ir = rcp(r);
     const T u = mx * ir, v = my * ir, w = mz * ir;
     const T p = c.gm1 * (e - c.half * (mx * u + my * v + mz * w));

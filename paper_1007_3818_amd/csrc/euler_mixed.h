@@ -23,6 +23,7 @@ struct MixedArith {
     // and nesting it gives the same value bitwise whenever a and b share a sign
     // (and 0 otherwise); only an a b that underflows to 0 would differ.
     static __device__ __forceinline__ float limiter(float a, float b, const Consts<float> &c) {
+#pragma clang fp contract(on)
         const float theta = c.theta;
         const float inner = __builtin_amdgcn_fmed3f(theta * b, 0.5f * (a + b), 0.0f);
         return __builtin_amdgcn_fmed3f(theta * a, inner, 0.0f);
@@ -40,6 +41,7 @@ struct MixedArith {
     template <int D>
     static __device__ __forceinline__ void char_slope(const float a[NV], const float b[NV], float h, float q, float cr, float c2,
                                                const Consts<float> &c, float dw[NV]) {
+#pragma clang fp contract(on)
         constexpr int N = 1 + D, T1 = D == 0 ? 2 : 1, T2 = D == 2 ? 2 : 3;
         const float m0 = limiter(q * a[4] - h * a[N], q * b[4] - h * b[N], c);
         const float m1 = limiter(a[0] - float(2) * q * a[4], b[0] - float(2) * q * b[4], c);

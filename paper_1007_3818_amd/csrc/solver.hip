@@ -171,6 +171,9 @@ static_assert(MAX_PARTS * sizeof(unsigned) <= NSTAT * sizeof(double), "a slot pe
 template <typename S_, typename T, int NT, int WAVES, bool PERIODIC, bool CHAR, bool SUB>
 __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT), amdgpu_waves_per_eu(WAVES, 8)))
 void solve_kernel(SolveParams<S_> P) {
+#pragma clang fp contract(on)
+    // (as in euler.h: the rounding is that of the source in every instantiation, so
+    // that a group's result does not depend on the batch that it is solved in)
     static_assert(NT == 320 || NT == 256, "work-group shape");
     constexpr bool SPLIT = NT == 320;
     // float at four waves per SIMD, 128 registers: what is loaded ahead or indexed twice
@@ -894,9 +897,8 @@ int choose_parts(int64_t n) {
 // default; grid <= 0 launches one work-group per group (or part of one, where
 // the caller leaves p.nsub at 0), grid > 0 a persistent grid that strides over
 // the groups.  Batches small enough to be split run the kernel that can split
-// (SUB) whatever the grid and zseg, so that these do not change the results (the
-// compiler may contract multiply-adds differently in the other one, which
-// spares large batches the parts' bookkeeping, 2% of a step).
+// (SUB) whatever the grid and zseg; the other one, with the same results, spares
+// large batches the parts' bookkeeping, 2% of a step.
 template <typename S_, typename T>
 hipError_t launch_solve(const SolveParams<S_> &params, int variant, int64_t grid, hipStream_t s) {
     SolveParams<S_> p = params;
