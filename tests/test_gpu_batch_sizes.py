@@ -2,7 +2,7 @@
 to 384 groups (float arithmetic) or 256 (double) run the kernel that can split a
 group in z, larger ones the one that cannot: the same groups on either side of that
 size give the same bits, state, flux planes, stats and fallback counts, for padded
-and for periodic input."""
+and for periodic input; and the two inputs give the same bits as each other."""
 import pytest
 import torch
 
@@ -71,3 +71,19 @@ def test_periodic(gpu, flow, dtype, compute, most, limiting):
                                    G53, limiting=limiting, compute=compute, **o)
         got.append({k: v.reshape(gz, gy, x, *v.shape[1:])[:, :, :gx] for k, v in o.items()})
     _same(got[0], got[1], "periodic")
+
+
+@pytest.mark.parametrize("limiting", ["primitive", "characteristic"])
+@pytest.mark.parametrize("dtype,compute,most", KINDS)
+def test_padded_equals_periodic(gpu, flow, dtype, compute, most, limiting):
+    """The default variant on either input, in a batch that is split and in one that is not."""
+    st, dh = flow
+    for gx, gy, gz in ((4, 4, 4), (8, 8, 8)):
+        n = gx * gy * gz
+        s = st[:n].to(dtype).contiguous()
+        dt = 0.1 * hydro.cfl_dt(st, dh, G53, 0.5)  # the cut-out grid has jumps at its ends
+        kw = dict(limiting=limiting, compute=compute)
+        a, b = _outputs(n, dtype, gpu), _outputs(n, dtype, gpu)
+        hydro.hydro_solve_periodic(s, gx, gy, gz, _one(dt, gpu), _one(dh, gpu), G53, **kw, **a)
+        hydro.hydro_solve_batched(hydro.pack_periodic(s, gx, gy, gz), None, _one(dt, gpu), _one(dh, gpu), G53, **kw, **b)
+        _same(a, b, (n, limiting))
