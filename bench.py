@@ -577,19 +577,25 @@ def bench_ctu(tag, state, g, dh, steps, warmup):
     return res
 
 
-RTVD_VALUES_PER_GROUP = 16 ** 3 + 2 * (16 * 22 * 22) + 2 * (16 * 16 * 22) + 16 ** 3
-# arithmetic of one sweep over a pencil of 22 cells (16 updated), counted as for
-# the MUSCL-Hancock model: relaxed fluxes (48 per cell) at 22 cells, half step
-# (35) and relaxed fluxes again at 20, second-order fluxes with the van Leer
-# limiter (110 per face) at 17 faces, the update (15) at 16 cells; pencils per
-# group and step: 22 x 22, 16 x 22 and 16 x 16
+def rtvd_launches(g):
+    """Launches of a periodic relaxing-TVD step of g^3 groups: x and y go together
+    where a thread of that sweep has two groups or more to march through, which the
+    library gives it when 1,024 work-groups are left (runs of up to 58
+    output cells along x, four z planes a work-group, 32 cells along y)."""
+    n = 16 * g
+    return 2 if g >= 2 and -(-n // 58) * 4 * g * -(-n // 32) >= 1024 else 3
+
+
+def rtvd_bytes_per_cell(g, elem):
+    """What those launches have to move: each reads and writes five values a cell."""
+    return 2 * 5 * elem * rtvd_launches(g)
 
 
 def bench_rtvd(tag, state, g, dh, steps, warmup):
-    """The relaxing TVD scheme on the same periodic grid: one step = three
-    sweep launches (ghost cells read in place by the first), alternating the
-    sweep order.  Algorithmic bytes per group: read the state once, write and
-    read the two intermediate blocks, write the result."""
+    """The relaxing TVD scheme on the same periodic grid: one step = three sweeps of
+    whole groups in two or three launches, alternating the sweep order, each
+    launch with its ghost cells read in place from the neighbouring groups.
+    Algorithmic bytes: the state read and written once by every launch."""
     import torch
     from paper_1007_3818_amd import hydro
 
@@ -619,15 +625,16 @@ def bench_rtvd(tag, state, g, dh, steps, warmup):
     cells = n * CELLS
     if not bool(torch.isfinite(cur).all()):
         return {"error": "non-finite values after the timed steps", "ms_per_step": ms}
-    b = RTVD_VALUES_PER_GROUP * 5 * state.element_size() * n
+    b = rtvd_bytes_per_cell(g, state.element_size()) * cells
     flops = RTVD_FLOPS_PER_CELL * cells
     return {"ms_per_step": ms, "cell_updates_per_s": cells / (ms * 1e-3),
             "algorithmic_bytes_per_cell": b / cells, "hbm_GBps": b / (ms * 1e-3) / 1e9,
             "hbm_frac": b / (ms * 1e-3) / HBM_PEAK,
             "flops_per_cell": RTVD_FLOPS_PER_CELL, "alu_TFLOPs": flops / (ms * 1e-3) / 1e12,
             "alu_frac": flops / (ms * 1e-3) / PEAK[tag],
-            "step": "three sweeps (x,y,z / z,y,x alternating), ghost cells read in place, CFL dt of "
-                    "the initial state"}
+            "launches_per_step": rtvd_launches(g),
+            "step": "three sweeps of whole groups (x,y,z / z,y,x alternating), x and y in one launch on "
+                    "large grids, ghost cells read in place, CFL dt of the initial state"}
 
 
 def neighbourhood(gid, g):
