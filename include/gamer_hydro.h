@@ -183,8 +183,8 @@ int gamer_hydro_solve_batched_f32(const float *groups_in, int64_t n_groups, cons
  * (The paper's Sec. 2 notes that preparing ghost zones costs more than the GPU
  * solver itself; for this uniform case the preparation disappears.)  Results
  * equal those of gamer_pack_periodic followed by the batched step with the
- * same variant: bitwise in FP64 with primitive limiting, to rounding otherwise
- * (the two are separate compilations, whose multiply-adds may contract
+ * same variant: bitwise with the default variant and in FP64, to rounding
+ * otherwise (the two are separate compilations, whose multiply-adds may contract
  * differently); fallback counts are equal.  dt_dev, dh_dev: device double
  * [1].  state_out must not be state.  group_stats, fluxes_out, opts as in the
  * batched step; opts->zseg as described with gamer_opts.

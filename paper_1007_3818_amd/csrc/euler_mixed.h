@@ -1,9 +1,13 @@
 // euler_mixed.h -- the float arithmetic of the FP64-state, FP32-arithmetic path:
-// limiters, Hancock predictor and Roe's flux of euler.h in an earlier order of
-// operations.  That path stores its result in double, where a float operation
-// taken in another order shows in the ninth digit; it keeps the order (and with
-// it the values) that its users have, while the other paths use the shorter
-// forms of euler.h.
+// limiters, Hancock predictor and Roe's flux in the order of operations that they
+// had before euler.h's shorter forms.  That path stores its result in double, where
+// a float operation taken in another order shows in the ninth digit.  With periodic
+// input its values are those of the earlier kernels bitwise.  With padded input the
+// default variant now gives the same bits as with periodic input, which it did not
+// before: up to 2e-8 of the state's norm in a flow of strong contrasts, half the
+// step's own error.  The predictor's and the fluxes' multiply-adds are the
+// compiler's choice (unlike those of euler.h, and of the limiters here): to fix them
+// by the source would move those values again.
 #pragma once
 
 #include "euler.h"

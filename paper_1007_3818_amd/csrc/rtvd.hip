@@ -1,7 +1,8 @@
 // rtvd.hip -- the relaxing TVD scheme (the solver the paper compares
-// MUSCL-Hancock with): three dimensionally split sweeps per step, one launch
-// per sweep, each advancing every pencil along the sweep direction by the
-// relaxing scheme's half step and full step.
+// MUSCL-Hancock with): three dimensionally split sweeps per step, each advancing
+// every pencil along the sweep direction by the relaxing scheme's half step and
+// full step.  The z sweep is a launch of its own; x and y take one launch together
+// on large inputs and one each on small ones (rtvd_xy, together()).
 //
 // Padded groups: the block shrinks by three cells per side along the sweep
 // direction only, so the three sweeps go 22^3 -> 16 x 22 x 22 -> 16 x 16 x 22 ->
@@ -312,7 +313,8 @@ constexpr int PREFETCH = 2;  // cells between a load's issue and its use (segmen
 // pencils along the fastest transverse axis.
 template <typename T, int D>
 __global__ __launch_bounds__(256) void rtvd_march_padded(SweepArgs<T> P) {
-    constexpr int A = D == 0 ? 1 : 0, B = D == 2 ? 1 : 2;  // transverse axes, A fastest
+    static_assert(D == 1 || D == 2, "y and z sweeps");
+    constexpr int A = 0, B = D == 2 ? 1 : 2;  // transverse axes, A fastest
     const int e[3] = {P.ex, P.ey, P.ez};
     int eo[3] = {P.ex, P.ey, P.ez};
     eo[D] -= 2 * RG;

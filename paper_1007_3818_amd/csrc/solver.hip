@@ -31,14 +31,17 @@
 //    they are used (`fresh`) instead of living across the sweep, and global
 //    accesses take a scalar base and a 32-bit lane offset (`at`).  With the forms
 //    of euler.h this took the double kernel from 9 spilled registers to none and
-//    the 256^3 padded step from 1,070 to 988 us (float: 577 -> 549 us).
+//    the 256^3 padded step from 1,070 to 988 us (float: 577 -> 549 us; 963 and 525 us
+//    with what came after).
 //  - The update of plane k-1 completes at step k, once the z flux above it is
 //    known: U - dt/dh ((dF_x + dF_y) + dF_z), in double for both precisions.
-//  - Plane k+2 is loaded into registers at the top of step k and written to
-//    the ring after the step's last barrier.  The old state of plane k-1 is
-//    loaded in one batch before the update's stores.  Both orderings keep the
-//    waits for loads from also waiting out earlier output stores (vector memory
-//    operations complete in issue order).
+//  - Plane k+2 is loaded into registers at the top of step k and written to the
+//    ring next to the barrier after the x and y faces: before it in float with 256
+//    threads (where a further barrier, once the fluxes are read, ends the step),
+//    after it otherwise.  The old state of plane k-1 is loaded in one batch before
+//    the update's stores.  Both orderings keep the waits for loads from also
+//    waiting out the step's output stores (vector memory operations complete in
+//    issue order).
 //  - Template parameters select the storage and arithmetic types (float,
 //    double, or double state with float arithmetic), the input (padded groups
 //    or a periodic grid of unpadded groups read in place) and the limited
@@ -520,9 +523,9 @@ void solve_kernel(SolveParams<S_> P) {
 
             // z face between planes k-1 and k (registers only).  A wave that
             // computed ghost-layer cells in this plane solves it after the x and
-            // y faces instead, while the two waves that take the faces 16 are
-            // busy with them, so that no wave does more than one cell and three
-            // Roe solves between two barriers.
+            // y faces instead, while the wave that takes the faces 16 is busy with
+            // them, so that no wave does more than one cell and three Roe solves
+            // between two barriers.
             T fzn[NV];
             auto solve_z = [&]() {
                 if (inner && k >= 0) {
@@ -881,9 +884,12 @@ namespace {
 // (a CU holds three float or two double work-groups).  A group's sweep is one
 // chain of 18 plane steps, about 5 us each however empty the chip is, and a
 // part of NI / s planes takes NI / s + 2 of them.  Measured per step (periodic,
-// reduce included): 8 groups FP64 150 -> 44 us in 8 parts; 64 groups FP32 100
-// -> 39 in 8; 125 groups FP64 122 -> 74 in 4 (81 in 8, which no longer fit);
-// 216 groups FP32 101 -> 74 in 2 (77 in 4); 512 groups FP32 116 -> 125 in 2.
+// reduce included), whole groups against the parts that the rule takes: 8 groups
+// FP64 110 and 26 us (16 parts), 64 groups FP32 97 and 33 (8), 125 groups FP64 112
+// and 60 (4), 216 groups FP32 98 and 69 (2), 384 groups FP32 109 and 83 (2), 256
+// groups FP64 113 and 95 (2).  More parts than have a slot lose: 125 groups FP64 81
+// us in 8 where 4 took 74, 216 groups FP32 77 in 4 against 74 in 2, 512 groups FP32
+// 125 in 2 against 116 whole (all with the slower stats and reduction of the time).
 template <typename T>
 int choose_parts(int64_t n) {
     constexpr int64_t slots = 256 * (sizeof(T) == 4 ? 3 : 2);
