@@ -780,7 +780,7 @@ def counter_pass(args, dev):
     hydro.group_stats(st, GAMMA, out=stats)
     hydro.step_reduce(stats, None, dh_dev, CFL, dt_out=dt_dev)
     # the relaxing TVD and the fused periodic step read the grid in place
-    pad_state = st if args.counter_kernel in ("rtvd", "periodic") else None
+    pad_state = st if args.counter_kernel in ("rtvd", "periodic", "mixed", "parts") else None
     del st
     out = torch.empty((g ** 3, 5, 16, 16, 16), dtype=pad.dtype, device=dev)
     v = args.variant or 0
@@ -792,6 +792,13 @@ def counter_pass(args, dev):
             hydro.hydro_solve_periodic(pad_state if k % 2 == 0 else out, g, g, g, dt_dev, dh_dev, GAMMA,
                                        out=out if k % 2 == 0 else pad_state, group_stats=stats, variant=v,
                                        grid=args.grid)
+        elif args.counter_kernel == "mixed":
+            hydro.hydro_solve_periodic(pad_state, g, g, g, dt_dev, dh_dev, GAMMA, out=out, group_stats=stats,
+                                       variant=v, compute=torch.float32)
+        elif args.counter_kernel == "parts":
+            # the first 64 groups as a grid of their own: each is swept in z parts
+            hydro.hydro_solve_periodic(pad_state[:64], 4, 4, 4, dt_dev, dh_dev, GAMMA, out=out[:64],
+                                       group_stats=stats[:64])
         elif args.counter_kernel == "ctu":
             hydro.ctu_solve_batched(pad, None, dt_dev, dh_dev, GAMMA, out=out, group_stats=stats,
                                     variant=hydro.CTU_FUSED)
@@ -825,9 +832,11 @@ def main():
                          "every dispatch, and the device generator issues thousands), copy it over, run a "
                          "plain 1 GiB device copy, then N batched solves of --dtype at --variant/--grid, "
                          "and exit without timing")
-    ap.add_argument("--counter-kernel", choices=["solve", "periodic", "ctu", "rtvd"], default="solve",
+    ap.add_argument("--counter-kernel", choices=["solve", "periodic", "mixed", "parts", "ctu", "rtvd"],
+                    default="solve",
                     help="with --counter-pass: the batched solver (default), the fused periodic step, the "
-                         "fused CTU step or the relaxing-TVD step (alternating sweep orders)")
+                         "same on FP64 state in FP32 arithmetic (--dtype f64), the same on 64 groups (swept in "
+                         "z parts), the fused CTU step or the relaxing-TVD step (alternating sweep orders)")
     ap.add_argument("--variant", type=int, default=None,
                     help="use this compiled solver variant (with --grid) instead of tuning")
     ap.add_argument("--grid", type=int, default=0, help="launch grid with --variant (0: one per group)")
