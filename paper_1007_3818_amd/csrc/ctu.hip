@@ -26,8 +26,8 @@
 // on their way to the next A.  With columns numbered row by row (six waves in
 // every phase, a third of E's lanes idle) and the plane stored after E, behind a
 // third barrier, a step of 256^3 took 1.480 ms in float and 3.553 ms in double,
-// against 1.384 and 3.056 ms; a SIMD has at most three waves in float and two in
-// double to hide a barrier with.
+// against 1.384 and 3.056 ms (1.377 and 2.88 ms with what came after); a SIMD has at
+// most three waves in float and two in double to hide a barrier with.
 // Nothing is written to memory but the result, the flux planes and the stats.
 //
 // The pipeline (variant 1) keeps its intermediate arrays in a caller-provided
@@ -553,8 +553,9 @@ void ctu_fused(CtuArgs<T> P) {
     int ii = i + NG, jj = j + NG;              // its padded position
     bool in_i = i >= 0 && i < NI, in_j = j >= 0 && j < NI;
     // The column taken afresh: in double, addresses and conditions formed before
-    // are not kept in registers past this place (256 and 52 bytes of scratch ->
-    // 240 and none).  In float, where they fit, it costs more than it frees.
+    // are not kept in registers past this place (256 and 52 bytes of scratch -> 240
+    // and none where it was taken; 256 and 16 with the Roe flux's two roots).  In
+    // float, where they fit, it costs more than it frees.
     constexpr bool F64 = sizeof(T) == 8;
     auto afresh = [&]() {
         if constexpr (F64) {
